@@ -15,24 +15,13 @@
 #include <cmath>
 #include <cstdint>
 
+#include "grouped.h"
 #include "kernels.h"
 
 namespace moecache {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kWave = 64;
-
-// MFMA operand and accumulator vectors.
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ float half_bits_to_float(uint32_t bits16) {
-  _Float16 h;
-  uint16_t b = (uint16_t)bits16;
-  __builtin_memcpy(&h, &b, 2);
-  return (float)h;
-}
 
 // (value, id) order used for routing: larger value first, lower id on ties.
 __device__ __forceinline__ bool better(float v, int id, float bv, int bid) {
@@ -1110,19 +1099,6 @@ __device__ __forceinline__ int plane_bytes(int n) { return (n / 64) * kPairPitch
 // Offset in a plane of the value at index i (any i; a 4-aligned i starts a dword).
 __device__ __forceinline__ int pad_off(int i) { return (i >> 6) * kPairPitch + (i & 63); }
 
-// A pair is only 4-byte aligned; the 16-byte loads below rely on the
-// unaligned global access that gfx9 runtimes enable (one dwordx4 instead of
-// four dword loads: a quarter of the address work per byte).
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
-// Weight pointers come out of the work lists as generic pointers; loads
-// through them would be flat loads, which also count against the LDS wait
-// counter (every LDS wait would then wait for the weights as well).  Slots
-// are device memory: the weights are read through global-address-space
-// pointers.
-typedef __attribute__((address_space(1))) const u32x4_a4 g_u32x4_a4;
-typedef __attribute__((address_space(1))) const uint32_t g_u32;
-
 template <int QT>
 __device__ __forceinline__ void load_pair(const uint8_t *p, uint32_t (&wd)[Fmt<QT>::kPairDwords]) {
   constexpr int PD = Fmt<QT>::kPairDwords;
@@ -1142,14 +1118,6 @@ __device__ __forceinline__ void load_pair(const uint8_t *p, uint32_t (&wd)[Fmt<Q
 __device__ __forceinline__ float recombine(int i1, int i2, int i3) {
   return fmaf((float)i3, 1.f / 64516.f, fmaf((float)i2, 1.f / 254.f, (float)i1));
 }
-
-// Four Q4_0 nibbles of a dword as signed bytes 16 (n - 8): bit 3 of the nibble
-// flipped makes it the 4-bit two's complement of n - 8, and at the top of its
-// byte (the other nibble cleared) the byte is 16 (n - 8).  q4_lo takes the low
-// nibble of each byte, q4_hi the high one; the flip of bit 7 after the shift
-// is the flip of bit 3 before it.
-__device__ __forceinline__ uint32_t q4_lo(uint32_t w) { return ((w << 4) & 0xf0f0f0f0u) ^ 0x80808080u; }
-__device__ __forceinline__ uint32_t q4_hi(uint32_t w) { return (w & 0xf0f0f0f0u) ^ 0x80808080u; }
 
 // Partial dot of one pair with the inputs: D[c][j] = digit plane c, dword j of
 // the pair's 64 inputs; sc0/sc1 the two input block scales.
@@ -2808,45 +2776,7 @@ __global__ __launch_bounds__(kThreads) void group_place_kernel(const int32_t *__
   }
 }
 
-// One wave's experts for the grouped GEMMs (kernel argument, about 3 KB).
-constexpr int kPfMaxExperts = 128;
-constexpr int kPfMaxTiles = 512;
-struct PfExperts {
-  const uint8_t *payload[kPfMaxExperts];
-  int32_t row0[kPfMaxExperts];  // first row of the expert's pairs in perm / Ab
-  int32_t n[kPfMaxExperts];     // pairs (tokens) routed to it
-  int32_t count;
-  // flat M-tile t (128 rows): expert in the low byte, the expert's M-tile in the
-  // high byte; ntiles == 0 when the launch's tiles do not fit (then a scan)
-  int32_t ntiles;
-  uint16_t tile[kPfMaxTiles];
-};
-
-constexpr int kPfBM = 128;  // tokens per tile
-constexpr int kPfBK = 64;   // one pair of weight blocks per row
 constexpr int kPfLd = kPfBK + 8;  // LDS row stride in bf16 (padding against bank conflicts)
-
-// (expert, M-tile) of a flat M-tile index; returns false past the end.  One
-// lookup in the launch's tile table (a scan over the experts, one dependent
-// scalar load each, took microseconds for the last tiles of a launch).
-__device__ __forceinline__ bool pf_tile(const PfExperts &X, int mt, int &j, int &m0) {
-  if (X.ntiles > 0) {
-    if (mt >= X.ntiles) return false;
-    const uint32_t v = X.tile[mt];
-    j = (int)(v & 0xffu);
-    m0 = (int)(v >> 8) * kPfBM;
-    return true;
-  }
-  for (j = 0; j < X.count; ++j) {
-    const int tiles = (X.n[j] + kPfBM - 1) / kPfBM;
-    if (mt < tiles) {
-      m0 = mt * kPfBM;
-      return true;
-    }
-    mt -= tiles;
-  }
-  return false;
-}
 
 // Dequantise one 32-weight block (half a pair) of a weight row to bf16.  The
 // thread loads the 9 dwords of its half of the pair: half 0 = bytes 0..35,
@@ -3055,24 +2985,6 @@ __global__ __launch_bounds__(kThreads, 2) void pf_gateup_kernel(PfGateUpParams a
       }
 }
 
-// SiLU for the grouped GEMMs' epilogue: the hardware base-2 exponential and
-// reciprocal (about 1 ulp each) instead of the library exp and an IEEE divide,
-// which took a fifth of a tile's time there.
-__device__ __forceinline__ float silu_fast(float s) {
-  return s * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * s));
-}
-
-typedef __attribute__((address_space(3))) void lds_void;
-typedef __attribute__((address_space(1))) const void g_void;
-
-// Direct global -> LDS load of 16 bytes per lane: lane l's bytes land at
-// dst + 16 l (dst wave-uniform).
-__device__ __forceinline__ void dma16(const void *g, void *dst) {
-  __builtin_amdgcn_global_load_lds((g_void *)g, (lds_void *)dst, 16, 0, 0);
-}
-
-constexpr int kPfWideThreads = 512;
-
 struct PfDownParams {
   PfExperts X;
   const int32_t *perm;
@@ -3177,29 +3089,7 @@ __global__ __launch_bounds__(kThreads, 2) void pf_down_kernel(PfDownParams a) {
 // once per 256 rows, ran no faster: the loop is bound by latency, not by the
 // dequantisation).
 constexpr int kGmThreads = 256;
-constexpr int kGmBM = 128;
 constexpr int kGmQ = 512 / kGmThreads;  // dequantised quarters per thread and step
-
-// (expert, M-tile) of a flat M-tile index with kGmBM-row tiles.
-__device__ __forceinline__ bool gm_tile(const PfExperts &X, int mt, int &j, int &m0) {
-  static_assert(kGmBM == kPfBM, "the tile table is built for 128-row tiles");
-  if (X.ntiles > 0) {
-    if (mt >= X.ntiles) return false;
-    const uint32_t v = X.tile[mt];
-    j = (int)(v & 0xffu);
-    m0 = (int)(v >> 8) * kGmBM;
-    return true;
-  }
-  for (j = 0; j < X.count; ++j) {
-    const int tiles = (X.n[j] + kGmBM - 1) / kGmBM;
-    if (mt < tiles) {
-      m0 = mt * kGmBM;
-      return true;
-    }
-    mt -= tiles;
-  }
-  return false;
-}
 
 // The raw bytes thread quarter bq (0..3) needs for K step kt of a weight row:
 //   Q8_0 (pair of blocks at 68 kt): the 9 dwords of block bq / 2 (load_half);
@@ -3324,17 +3214,6 @@ __device__ __forceinline__ void gm_dequant(const uint32_t (&v)[12], const uint8_
   *reinterpret_cast<uint4 *>(dst + 8) = *reinterpret_cast<const uint4 *>(o + 8);
 }
 
-struct GmParams {
-  PfExperts X;
-  const int32_t *perm;
-  const __bf16 *A;  // gate/up: xb [2][T][H]; down: ab [2][pairs][I] (hi then lo planes)
-  __bf16 *ab;       // gate/up output [2][pairs][I]
-  const float *w;   // down: routing weights [pairs]
-  float *P;         // down output [pairs][H]
-  int T, pairs, H, I, k;
-  int64_t mat, down_off;  // bytes of W_gate; offset of W_down in a payload
-  int64_t rowb;           // bytes of a weight row of the format (gate/up: H inputs; down: I)
-};
 // kernel arguments stay within 4 KB
 static_assert(sizeof(GmParams) <= 4096 && sizeof(PfGateUpParams) <= 4096 && sizeof(PfDownParams) <= 4096,
               "grouped-GEMM kernel arguments exceed 4 KB");
@@ -3346,7 +3225,7 @@ template <int FMT>
 __global__ __launch_bounds__(kGmThreads, 512 / kGmThreads) void gm_gateup_kernel(GmParams a) {
   __shared__ __align__(16) __bf16 Bs[3][128][kPfLd];
   int j, m0;
-  if (!gm_tile(a.X, blockIdx.x, j, m0)) return;
+  if (!pf_tile(a.X, blockIdx.x, j, m0)) return;
   const int n0 = blockIdx.y * 64;
   const int n = a.X.n[j], row0 = a.X.row0[j];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
@@ -3431,7 +3310,7 @@ template <int FMT>
 __global__ __launch_bounds__(kGmThreads, 512 / kGmThreads) void gm_down_kernel(GmParams a) {
   __shared__ __align__(16) __bf16 Bs[3][128][kPfLd];
   int j, m0;
-  if (!gm_tile(a.X, blockIdx.x, j, m0)) return;
+  if (!pf_tile(a.X, blockIdx.x, j, m0)) return;
   const int n0 = blockIdx.y * 128;
   const int n = a.X.n[j], row0 = a.X.row0[j];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
@@ -3952,379 +3831,10 @@ hipError_t launch_group(const int32_t *idx, int npairs, int E, int32_t *counts, 
   return hipGetLastError();
 }
 
-// The wave's experts and the M-tile count of 256-row tiles.
-// ------------------------------------------------ wide-tile grouped GEMMs ---
-//
-// One block per (M-tile of 128 rows, 256 columns), 512 threads: waves 0-3
-// multiply (wave c: tile rows 32c..32c+31 against all 256 weight columns, the
-// MFMA sequence per accumulator of pf_gateup_kernel / pf_down_kernel), waves
-// 4-7 stage the next K step of 64: the activation tile (both planes) by direct
-// global -> LDS loads, each 8 lanes one full 128-byte row segment with its
-// 16-byte chunks XOR-swizzled by row (so the MFMA operand reads hit distinct
-// banks), and the weight tile dequantised from the raw bytes of one weight row
-// per thread, loaded a step ahead.  Each LDS stage is its own array, so that
-// the compiler sees the reads of one stage not alias the loads into the other.
-// The 1-D grid runs the column tiles of an M-tile, then an expert's M-tiles, one
-// after the other on the same XCD (block L runs on XCD L % 8), so that their
-// shared activation rows and weights come from that XCD's L2.
-//
-// A producer thread's raw bytes of one K step (64 weights of its row):
-//   Q8_0 / Q4_0: the pair of blocks (17 / 9 dwords);
-//   Q4_K / Q6_K: the four 16-weight quarters as gm_load_raw takes them.
-//   Q6_K: the 64 bytes of ql, 32 of qh, the 4 scales and d that the step's 64
-//     weights use, as aligned dwords around them (see wide_dequant).
-template <int FMT>
-struct WideRaw {
-  static constexpr int kDw = FMT == 8 ? 17 : FMT == 2 ? 9 : FMT == 14 ? 19 : 48;
-};
-
-// K order of the wide kernels' steps.  A step multiplies 64 inputs; the sum
-// over K does not depend on the order in which they are visited, so a format
-// may visit them in the order its bytes hold them, as long as the activation
-// tile and the weight tile use the same one.  Step kt, 16-byte chunk c of the
-// step (eight inputs) covers K indices wide_kbase(kt) + wide_kchunk(c) + 0..7.
-// Q6_K: a step is one quarter (n, j) of a super-block, n = the half (128
-// weights), j = which 16 of each of its four 32-weight groups: the weights
-// 128 n + 32 g + 16 j + l (g < 4, l < 16), whose low bits sit in 16 bytes of
-// ql for g = 0, 2 (low and high nibbles), 16 bytes for g = 1, 3, and whose high
-// bits sit in 16 bytes of qh (two bits per group).  So every loaded byte is
-// used, once.  Tile position 16 g + l holds weight 128 n + 32 g + 16 j + l.
-template <int FMT>
-__device__ __forceinline__ uint32_t wide_kbase(int kt) {
-  if constexpr (FMT == 14) return 256u * (uint32_t)(kt >> 2) + 128u * (uint32_t)((kt >> 1) & 1) + 16u * (uint32_t)(kt & 1);
-  return (uint32_t)(kt * kPfBK);
-}
-template <int FMT>
-__device__ __forceinline__ uint32_t wide_kchunk(int c) {
-  if constexpr (FMT == 14) return 32u * (uint32_t)(c >> 1) + 8u * (uint32_t)(c & 1);
-  return 8u * (uint32_t)c;
-}
-template <int FMT>
-__device__ __forceinline__ void wide_load(const uint8_t *row, int kt, uint32_t (&v)[WideRaw<FMT>::kDw]) {
-  if constexpr (FMT == 8 || FMT == 2) {
-    const uint32_t *q = reinterpret_cast<const uint32_t *>(row + (int64_t)kt * 2 * Fmt<FMT>::kBlockBytes);
-#pragma unroll
-    for (int i = 0; i < WideRaw<FMT>::kDw; ++i) v[i] = q[i];
-  } else if constexpr (FMT == 14) {
-    // step kt: quarter (n, j) = ((kt / 2) % 2, kt % 2) of super-block kt / 4
-    // (210 bytes, 2-byte aligned; a: its address rounded down to a dword).  Its
-    // bytes: ql[64 n + 16 j, +16), ql[64 n + 32 + 16 j, +16), qh[32 n + 16 j, +16),
-    // scales 8 n + j + 2 g, d.  Loaded: five dwords from each of a + 64 n + 16 j,
-    // a + 64 n + 32 + 16 j and a + 128 + 32 n + 16 j (16 bytes plus the 2 of a
-    // misaligned start), three from a + 192 + 8 n, the one at a + 208 (d).  The
-    // furthest byte is a + 211, inside the payload: a payload ends 16-byte
-    // aligned, so its last super-block starts at an address 2 mod 4 and ends at
-    // a + 212.
-    const uint8_t *b = row + (int64_t)(kt >> 2) * 210;
-    const uint8_t *a = b - ((uintptr_t)b & 3);
-    const int n = (kt >> 1) & 1, j = kt & 1;
-    const uint8_t *run[3] = {a + 64 * n + 16 * j, a + 64 * n + 32 + 16 * j, a + 128 + 32 * n + 16 * j};
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-      const u32x4 q = *(g_u32x4_a4 *)run[r];
-      v[5 * r] = q.x;
-      v[5 * r + 1] = q.y;
-      v[5 * r + 2] = q.z;
-      v[5 * r + 3] = q.w;
-      v[5 * r + 4] = ((const g_u32 *)run[r])[4];
-    }
-    const g_u32 *sc = (const g_u32 *)(a + 192 + 8 * n);
-    v[15] = sc[0];
-    v[16] = sc[1];
-    v[17] = sc[2];
-    v[18] = *(const g_u32 *)(a + 208);
-  } else {
-#pragma unroll
-    for (int bq = 0; bq < 4; ++bq) {
-      uint32_t t[12];
-      gm_load_raw<FMT>(row, kt, bq, t);
-#pragma unroll
-      for (int i = 0; i < 12; ++i) v[12 * bq + i] = t[i];
-    }
-  }
-}
-// The row's 64 weights of step kt as bf16 into dst (16-byte aligned).
-template <int FMT>
-__device__ __forceinline__ void wide_dequant(const uint32_t (&v)[WideRaw<FMT>::kDw], const uint8_t *row,
-                                             int kt, __bf16 *dst) {
-  if constexpr (FMT == 8 || FMT == 2) {
-    constexpr int PW = WideRaw<FMT>::kDw, o1 = FMT == 8 ? 8 : 4;
-    uint32_t h0[9], h1[9];
-#pragma unroll
-    for (int i = 0; i < 9; ++i) {
-      h0[i] = i < PW ? v[i] : 0u;
-      h1[i] = i + o1 < PW ? v[i + o1] : 0u;
-    }
-    dequant_half<FMT>(h0, 0, dst);
-    dequant_half<FMT>(h1, 1, dst + 32);
-  } else if constexpr (FMT == 14) {
-    // Q6_K weight 128 n + 32 g + 16 j + l of the step (tile position 16 g + l):
-    // low four bits from ql run g % 2 (low nibbles for g < 2, high for g >= 2),
-    // high two bits from bits 2 g, 2 g + 1 of qh byte l, scale 8 n + 2 g + j.
-    // Four 6-bit q are assembled per dword (one per byte); each weight is
-    // ds (q - 32) = fma(ds, q, -32 ds) rounded once (32 ds is exact), as the
-    // quarter dequantiser forms it.
-    const int sh = (int)((uintptr_t)(row + (int64_t)(kt >> 2) * 210) & 3), j = kt & 1;
-    const uint64_t sc8 = (uint64_t)__builtin_amdgcn_alignbyte(v[17], v[16], sh) << 32 |
-                         __builtin_amdgcn_alignbyte(v[16], v[15], sh);
-    const float d = half_bits_to_float((v[18] >> (8 * sh)) & 0xffffu);
-    float ds[4];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) ds[g] = d * (float)(int8_t)((sc8 >> (8 * (2 * g + j))) & 0xffu);
-    __bf16 o[64];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t lA = __builtin_amdgcn_alignbyte(v[i + 1], v[i], sh);
-      const uint32_t lB = __builtin_amdgcn_alignbyte(v[6 + i], v[5 + i], sh);
-      const uint32_t hq = __builtin_amdgcn_alignbyte(v[11 + i], v[10 + i], sh);
-      const uint32_t q[4] = {(lA & 0x0f0f0f0fu) | ((hq << 4) & 0x30303030u),
-                             (lB & 0x0f0f0f0fu) | ((hq << 2) & 0x30303030u),
-                             ((lA >> 4) & 0x0f0f0f0fu) | (hq & 0x30303030u),
-                             ((lB >> 4) & 0x0f0f0f0fu) | ((hq >> 2) & 0x30303030u)};
-#pragma unroll
-      for (int g = 0; g < 4; ++g)
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-          o[16 * g + 4 * i + b] = (__bf16)fmaf(ds[g], (float)((q[g] >> (8 * b)) & 0xffu), -32.f * ds[g]);
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-      *reinterpret_cast<uint4 *>(dst + 8 * i) = *reinterpret_cast<const uint4 *>(o + 8 * i);
-  } else {
-#pragma unroll
-    for (int bq = 0; bq < 4; ++bq) {
-      uint32_t t[12];
-#pragma unroll
-      for (int i = 0; i < 12; ++i) t[i] = v[12 * bq + i];
-      gm_dequant<FMT>(t, row, kt, bq, dst + 16 * bq);
-    }
-  }
-}
-
-// The (M-tile, column tile) of this block in the XCD-grouped order.
-__device__ __forceinline__ void wide_tile(int NT, int &mt, int &nt) {
-  const int total = gridDim.x, L = blockIdx.x, x = L % 8, idx = L / 8, per = total / 8, rem = total % 8;
-  const int w = x * per + min(x, rem) + idx;
-  mt = w / NT;
-  nt = w % NT;
-}
-
-// Producer waves' K loop: stage kt + 1 while the consumers multiply kt.
-// asrc[u]: element offset (into the activation planes) of this lane's 16 bytes
-// in DMA instruction u; row: the thread's weight row.
-template <int FMT>
-__device__ __forceinline__ void wide_produce(const __bf16 *Abase, const uint32_t (&asrc)[8], const uint8_t *row,
-                                            int KT, int pw, int pt, __bf16 (*As0)[128][64],
-                                            __bf16 (*As1)[128][64], __bf16 (*Bs0)[kPfLd],
-                                            __bf16 (*Bs1)[kPfLd]) {
-  auto aload = [&](int kt, __bf16 (*As)[128][64]) {
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int g = 8 * pw + u;
-      dma16(Abase + (asrc[u] + wide_kbase<FMT>(kt)), &As[g >> 4][8 * (g & 15)][0]);
-    }
-  };
-  uint32_t B0[WideRaw<FMT>::kDw], B1[WideRaw<FMT>::kDw];
-  aload(0, As0);
-  wide_load<FMT>(row, 0, B0);
-  wide_load<FMT>(row, min(1, KT - 1), B1);
-  wide_dequant<FMT>(B0, row, 0, &Bs0[pt][0]);
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  // step kt: stage kt + 1 into the other arrays; the raw weights of kt + 1 are
-  // in BO, BS takes those of kt + 2
-#define WIDE_PROD(BS, BO, AN, BN, kt)                          \
-  do {                                                         \
-    if ((kt) + 1 < KT) {                                       \
-      aload((kt) + 1, AN);                                     \
-      wide_load<FMT>(row, min((kt) + 2, KT - 1), BS);          \
-      wide_dequant<FMT>(BO, row, (kt) + 1, &BN[pt][0]);        \
-    }                                                          \
-    __builtin_amdgcn_s_waitcnt(0);                             \
-    __syncthreads();                                           \
-  } while (0)
-  int kt = 0;
-  for (; kt + 2 <= KT; kt += 2) {
-    WIDE_PROD(B0, B1, As1, Bs1, kt);
-    WIDE_PROD(B1, B0, As0, Bs0, kt + 1);
-  }
-  if (kt < KT) WIDE_PROD(B0, B1, As1, Bs1, kt);
-#undef WIDE_PROD
-}
-
-// Consumer MFMAs of one K step: wave wv's 32 rows against NQ 16-column subtiles
-// of each of the NB weight groups (gate/up: NB 2 groups of 8; down: 1 of 16).
-template <int NB, int NQ>
-__device__ __forceinline__ void wide_mma(f32x4 (&acc)[NB][2][NQ], __bf16 (*As)[128][64], __bf16 (*Bs)[kPfLd],
-                                         int wv, int lane) {
-#pragma unroll
-  for (int ks = 0; ks < 2; ++ks) {
-    bf16x8 Ar[2][2];
-#pragma unroll
-    for (int pl = 0; pl < 2; ++pl)
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int r = 32 * wv + 16 * i + (lane & 15);
-        const int c = (4 * ks + (lane >> 4)) ^ (r & 7);
-        Ar[pl][i] = *reinterpret_cast<const bf16x8 *>(&As[pl][r][8 * c]);
-      }
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const int c = 32 * ks + 8 * (lane >> 4);
-      bf16x8 bf[NB];
-#pragma unroll
-      for (int b = 0; b < NB; ++b)
-        bf[b] = *reinterpret_cast<const bf16x8 *>(&Bs[128 * b + 16 * q + (lane & 15)][c]);
-#pragma unroll
-      for (int pl = 0; pl < 2; ++pl)
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int b = 0; b < NB; ++b)
-            acc[b][i][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ar[pl][i], bf[b], acc[b][i][q], 0, 0, 0);
-    }
-  }
-}
-
-// Gate/up (I a multiple of 128): weight rows 0..127 of the tile are W_gate rows
-// n0 .. n0+127, rows 128..255 the same rows of W_up; h = silu(g) u written as bf16
-// hi and lo terms at the pair's grouped row.
-template <int FMT>
-__global__ __launch_bounds__(kPfWideThreads, 1) void pf_gateup_wide_kernel(GmParams a) {
-  __shared__ __align__(16) __bf16 As0[2][128][64], As1[2][128][64];  // [plane][row][k], swizzled
-  __shared__ __align__(16) __bf16 Bs0[256][kPfLd], Bs1[256][kPfLd];
-  int mt, nt, j, m0;
-  wide_tile(a.I / 128, mt, nt);
-  if (!gm_tile(a.X, mt, j, m0)) return;
-  const int n0 = nt * 128;
-  const int n = a.X.n[j], row0 = a.X.row0[j];
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
-  const int KT = a.H / kPfBK;
-  if (wv >= 4) {
-    const int pw = wv - 4, pt = tid - 256;
-    const uint8_t *row = a.X.payload[j] + (pt >= 128 ? a.mat : 0) + (int64_t)(n0 + (pt & 127)) * a.rowb;
-    // DMA instruction g = 8 pw + u: plane g / 16, tile rows 8 (g % 16) .. +7;
-    // element offsets into xb (32 bits, checked at launch)
-    uint32_t asrc[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int g = 8 * pw + u, p = g >> 4, r = 8 * (g & 15) + (lane >> 3);
-      const int m = min(m0 + r, n - 1);
-      const int c = (lane & 7) ^ (lane >> 3);
-      asrc[u] = (uint32_t)p * (uint32_t)(a.T * a.H) + (uint32_t)(a.perm[row0 + m] / a.k) * (uint32_t)a.H +
-                wide_kchunk<FMT>(c);
-    }
-    wide_produce<FMT>(a.A, asrc, row, KT, pw, pt, As0, As1, Bs0, Bs1);
-    return;
-  }
-  f32x4 acc[2][2][8];  // [gate, up][i][q]
-#pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int q = 0; q < 8; ++q) acc[b][i][q] = f32x4{0.f, 0.f, 0.f, 0.f};
-  __syncthreads();
-  int kt = 0;
-  for (; kt + 2 <= KT; kt += 2) {
-    wide_mma<2, 8>(acc, As0, Bs0, wv, lane);
-    __syncthreads();
-    wide_mma<2, 8>(acc, As1, Bs1, wv, lane);
-    __syncthreads();
-  }
-  if (kt < KT) {
-    wide_mma<2, 8>(acc, As0, Bs0, wv, lane);
-    __syncthreads();
-  }
-  const int64_t plane = (int64_t)a.pairs * a.I;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int q = 0; q < 8; ++q)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = m0 + 32 * wv + 16 * i + 4 * (lane >> 4) + r;
-        if (m < n) {
-          const float v = silu_fast(acc[0][i][q][r]) * acc[1][i][q][r];
-          const __bf16 hi = (__bf16)v;
-          const int64_t o = (int64_t)(row0 + m) * a.I + n0 + 16 * q + (lane & 15);
-          a.ab[o] = hi;
-          a.ab[plane + o] = (__bf16)(v - (float)hi);
-        }
-      }
-}
-
-// Down (H a multiple of 256): weight rows are W_down rows n0 .. n0+255; the
-// activation rows are the expert's, contiguous in perm order; P[pair] = w * row.
-template <int FMT>
-__global__ __launch_bounds__(kPfWideThreads, 1) void pf_down_wide_kernel(GmParams a) {
-  __shared__ __align__(16) __bf16 As0[2][128][64], As1[2][128][64];
-  __shared__ __align__(16) __bf16 Bs0[256][kPfLd], Bs1[256][kPfLd];
-  int mt, nt, j, m0;
-  wide_tile(a.H / 256, mt, nt);
-  if (!gm_tile(a.X, mt, j, m0)) return;
-  const int n0 = nt * 256;
-  const int n = a.X.n[j], row0 = a.X.row0[j];
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
-  const int KT = a.I / kPfBK;
-  if (wv >= 4) {
-    const int pw = wv - 4, pt = tid - 256;
-    const uint8_t *row = a.X.payload[j] + a.down_off + (int64_t)(n0 + pt) * a.rowb;
-    uint32_t asrc[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int g = 8 * pw + u, p = g >> 4, r = 8 * (g & 15) + (lane >> 3);
-      const int m = min(m0 + r, n - 1);
-      const int c = (lane & 7) ^ (lane >> 3);
-      asrc[u] = (uint32_t)p * (uint32_t)(a.pairs * a.I) + (uint32_t)(row0 + m) * (uint32_t)a.I +
-                wide_kchunk<FMT>(c);
-    }
-    wide_produce<FMT>(a.A, asrc, row, KT, pw, pt, As0, As1, Bs0, Bs1);
-    return;
-  }
-  f32x4 acc[1][2][16];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int q = 0; q < 16; ++q) acc[0][i][q] = f32x4{0.f, 0.f, 0.f, 0.f};
-  __syncthreads();
-  int kt = 0;
-  for (; kt + 2 <= KT; kt += 2) {
-    wide_mma<1, 16>(acc, As0, Bs0, wv, lane);
-    __syncthreads();
-    wide_mma<1, 16>(acc, As1, Bs1, wv, lane);
-    __syncthreads();
-  }
-  if (kt < KT) {
-    wide_mma<1, 16>(acc, As0, Bs0, wv, lane);
-    __syncthreads();
-  }
-  // the lane's 8 output rows: pair ids, then their weights
-  int pair[2][4];
-  float wt[2][4];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      pair[i][r] = a.perm[row0 + min(m0 + 32 * wv + 16 * i + 4 * (lane >> 4) + r, n - 1)];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) wt[i][r] = a.w[pair[i][r]];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int m = m0 + 32 * wv + 16 * i + 4 * (lane >> 4) + r;
-      if (m < n) {
-        float *dst = a.P + (int64_t)pair[i][r] * a.H + n0 + (lane & 15);
-#pragma unroll
-        for (int q = 0; q < 16; ++q) dst[16 * q] = wt[i][r] * acc[0][i][q][r];
-      }
-    }
-}
-
-static int gm_experts(const PfWave &W, PfExperts &X) {
+// The launch's experts and their M-tiles of at most bm rows.  An expert of n rows
+// takes ceil(n / bm) tiles of equal rows, rounded up to 16 (128-row tiles, whose
+// kernels do the full tile's work whatever its rows, are left full).
+static int gm_experts(const PfWave &W, int bm, PfExperts &X) {
   X.count = W.count;
   int tiles = 0;
   bool table = true;
@@ -4332,7 +3842,10 @@ static int gm_experts(const PfWave &W, PfExperts &X) {
     X.payload[i] = W.payload[i];
     X.row0[i] = W.row0[i];
     X.n[i] = W.n[i];
-    const int ti = (W.n[i] + kGmBM - 1) / kGmBM;
+    const int even = (W.n[i] + bm - 1) / bm;
+    const int rt = bm == kWideBM && even > 0 ? ((W.n[i] + even - 1) / even + 15) / 16 * 16 : bm;
+    const int ti = (W.n[i] + rt - 1) / rt;
+    X.rt[i] = (int16_t)rt;
     if (ti > 256 || tiles + ti > kPfMaxTiles) table = false;
     for (int m = 0; table && m < ti; ++m) X.tile[tiles + m] = (uint16_t)(i | (m << 8));
     tiles += ti;
@@ -4374,21 +3887,28 @@ template <int F>
 struct GmDown {
   static auto fn() { return gm_down_kernel<F>; }
 };
-template <int F>
-struct WideGateUp {
-  static auto fn() { return pf_gateup_wide_kernel<F>; }
-};
-template <int F>
-struct WideDown {
-  static auto fn() { return pf_down_wide_kernel<F>; }
-};
+// The wide-tile kernels of a format.
+static hipError_t wide_launch(bool down, int fmt, dim3 g, const GmParams &a, hipStream_t s, const Timing &t) {
+  // the slim kernels where every tile of the launch has at most their 64 rows
+  bool slim = true;
+  for (int i = 0; i < a.X.count; ++i) slim = slim && a.X.rt[i] <= kSlimBM;
+  switch (fmt) {
+    case 8: return down ? wide_down<8>(slim, g, a, s, t) : wide_gateup<8>(slim, g, a, s, t);
+    case 2: return down ? wide_down<2>(slim, g, a, s, t) : wide_gateup<2>(slim, g, a, s, t);
+    case 12: return down ? wide_down<12>(slim, g, a, s, t) : wide_gateup<12>(slim, g, a, s, t);
+    case 14: return down ? wide_down<14>(slim, g, a, s, t) : wide_gateup<14>(slim, g, a, s, t);
+    default: return hipErrorInvalidValue;
+  }
+}
 
 hipError_t launch_pf_gateup(int qtype, const PfWave &W, const int32_t *perm, const __bf16 *xb,
                             __bf16 *ab, int T, int H, int I, int k, hipStream_t s, const Timing &t) {
   if (W.count < 0 || W.count > kPfMaxExperts) return hipErrorInvalidValue;
   GmParams a{};
-  const int tiles = gm_experts(W, a.X);
   const int fmt = fmt_gate_up(qtype);
+  // wide tiles, every format: element offsets into both activation planes have to fit 32 bits
+  const bool wide = I % 128 == 0 && H % 64 == 0 && H >= 3 * kPfBK && 2 * (int64_t)T * H <= (int64_t)UINT32_MAX;
+  const int tiles = gm_experts(W, wide ? kWideBM : kPfBM, a.X);
   a.perm = perm;
   a.A = xb;
   a.ab = ab;
@@ -4402,16 +3922,13 @@ hipError_t launch_pf_gateup(int qtype, const PfWave &W, const int32_t *perm, con
   if (tiles == 0) return hipSuccess;
   // the kernel indexes the activation planes in 16-byte units with 32 bits
   if (2 * (int64_t)T * H / 8 > (int64_t)UINT32_MAX || I % 64 || H % 64) return hipErrorInvalidValue;
-  if (I % 128 == 0 && 2 * (int64_t)T * H <= (int64_t)UINT32_MAX) {
-    // wide tiles, every format; element offsets into both activation planes fit 32 bits
+  if (wide) {
     const dim3 g((unsigned)tiles * (unsigned)(I / 128));
-    return gm_launch<WideGateUp>(fmt, g, a, s, t, kPfWideThreads);
+    return wide_launch(false, fmt, g, a, s, t);
   }
   if (fmt == 8 || fmt == 2) {  // the 32-weight block formats: pf_gateup_kernel (measured faster)
     PfGateUpParams b{};
     b.X = a.X;
-    int tl = 0;
-    for (int i = 0; i < W.count; ++i) tl += (W.n[i] + kPfBM - 1) / kPfBM;
     b.perm = perm;
     b.xb = xb;
     b.ab = ab;
@@ -4421,9 +3938,9 @@ hipError_t launch_pf_gateup(int qtype, const PfWave &W, const int32_t *perm, con
     b.I = I;
     b.k = k;
     if (fmt == 8)
-      hipExtLaunchKernelGGL(pf_gateup_kernel<8>, dim3(tl, I / 64), dim3(kThreads), 0, s, t.start, t.stop, 0, b);
+      hipExtLaunchKernelGGL(pf_gateup_kernel<8>, dim3(tiles, I / 64), dim3(kThreads), 0, s, t.start, t.stop, 0, b);
     else
-      hipExtLaunchKernelGGL(pf_gateup_kernel<2>, dim3(tl, I / 64), dim3(kThreads), 0, s, t.start, t.stop, 0, b);
+      hipExtLaunchKernelGGL(pf_gateup_kernel<2>, dim3(tiles, I / 64), dim3(kThreads), 0, s, t.start, t.stop, 0, b);
     return hipGetLastError();
   }
   return gm_launch<GmGateUp, false>(fmt, dim3(tiles, I / 64), a, s, t);
@@ -4434,8 +3951,10 @@ hipError_t launch_pf_down(int qtype, const PfWave &W, const int32_t *perm, const
                           const Timing &t) {
   if (W.count < 0 || W.count > kPfMaxExperts) return hipErrorInvalidValue;
   GmParams a{};
-  const int tiles = gm_experts(W, a.X);
   const int fmt = fmt_down(qtype);
+  // wide tiles, every format: element offsets into both activation planes have to fit 32 bits
+  const bool wide = H % 256 == 0 && I % 64 == 0 && I >= 3 * kPfBK && 2 * (int64_t)pairs * I <= (int64_t)UINT32_MAX;
+  const int tiles = gm_experts(W, wide ? kWideBM : kPfBM, a.X);
   a.perm = perm;
   a.A = ab;
   a.w = w;
@@ -4447,16 +3966,13 @@ hipError_t launch_pf_down(int qtype, const PfWave &W, const int32_t *perm, const
   a.down_off = 2 * fmt_matrix_bytes(fmt_gate_up(qtype), I, H);
   if (tiles == 0) return hipSuccess;
   if (2 * (int64_t)pairs * I / 8 > (int64_t)UINT32_MAX || I % 64 || H % 64) return hipErrorInvalidValue;
-  if (H % 256 == 0 && 2 * (int64_t)pairs * I <= (int64_t)UINT32_MAX) {
-    // wide tiles, every format; element offsets into both activation planes fit 32 bits
+  if (wide) {
     const dim3 g((unsigned)tiles * (unsigned)(H / 256));
-    return gm_launch<WideDown>(fmt, g, a, s, t, kPfWideThreads);
+    return wide_launch(true, fmt, g, a, s, t);
   }
   if (fmt == 8 || fmt == 2) {
     PfDownParams b{};
     b.X = a.X;
-    int tl = 0;
-    for (int i = 0; i < W.count; ++i) tl += (W.n[i] + kPfBM - 1) / kPfBM;
     b.perm = perm;
     b.ab = ab;
     b.w = w;
@@ -4465,9 +3981,9 @@ hipError_t launch_pf_down(int qtype, const PfWave &W, const int32_t *perm, const
     b.H = H;
     b.I = I;
     if (fmt == 8)
-      hipExtLaunchKernelGGL(pf_down_kernel<8>, dim3(tl, (H + 127) / 128), dim3(kThreads), 0, s, t.start, t.stop, 0, b);
+      hipExtLaunchKernelGGL(pf_down_kernel<8>, dim3(tiles, (H + 127) / 128), dim3(kThreads), 0, s, t.start, t.stop, 0, b);
     else
-      hipExtLaunchKernelGGL(pf_down_kernel<2>, dim3(tl, (H + 127) / 128), dim3(kThreads), 0, s, t.start, t.stop, 0, b);
+      hipExtLaunchKernelGGL(pf_down_kernel<2>, dim3(tiles, (H + 127) / 128), dim3(kThreads), 0, s, t.start, t.stop, 0, b);
     return hipGetLastError();
   }
   return gm_launch<GmDown, false>(fmt, dim3(tiles, (H + 127) / 128), a, s, t);

@@ -1,0 +1,724 @@
+// The grouped GEMMs' wide-tile kernels (a multi-token call's gate/up and down over
+// many rows per expert), templates over the weight format; each format is its own
+// translation unit (wide_*.hip), so that they compile side by side.
+#pragma once
+#include <type_traits>
+
+#include "grouped.h"
+
+namespace moecache {
+namespace {
+
+// SiLU for the grouped GEMMs' epilogue: the hardware base-2 exponential and
+// reciprocal (about 1 ulp each) instead of the library exp and an IEEE divide,
+// which took a fifth of a tile's time there.
+__device__ __forceinline__ float silu_fast(float s) {
+  return s * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * s));
+}
+
+typedef __attribute__((address_space(3))) void lds_void;
+
+// Direct global -> LDS load of 16 bytes per lane from a buffer: lane l's bytes, at
+// byte offset off + base of the buffer (off per lane, base uniform), land at
+// dst + 16 l (dst wave-uniform).  (The buffer form: after a flat-encoded direct load
+// the compiler takes every later wait for a loaded register as a wait for all.)
+__device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t buf, uint32_t off, uint32_t base, void *dst) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(buf, (lds_void *)dst, 16, (int)off, (int)base, 0, 0);
+}
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t wide_buffer(const void *p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
+}
+
+// Two kernels for each of gate/up and down, both over tiles of rows x 256 weight rows
+// with K steps of 64.  The activation tile (both planes) goes straight from global
+// memory into LDS with direct loads.  Every multiplying wave takes all of a tile's rows
+// in 16-row subtiles against 64 of its 256 weight rows, so a tile's MFMAs follow its
+// rows.  An expert's rows are split evenly over ceil(n / 144) tiles.
+//   wide (tiles of up to 144 rows): 512 threads, one block per CU.  Waves 0-3 multiply
+//     the current step, waves 4-7 stage the next one: the direct loads and the weight
+//     tile, dequantised into LDS.
+//   slim (launches whose tiles have at most 64 rows): 256 threads, two blocks per CU.
+//     Each wave loads and dequantises its own 64 weight rows into its MFMA operand
+//     registers (nothing of a weight goes through LDS), with the loads of later steps
+//     in flight and the activations two steps ahead in three LDS stages.
+// The line between them lies at 64 rows: a wave's vector instructions do not hide behind
+// its own MFMAs (one block of the slim kind per CU on 144-row tiles took 563 us where
+// wide takes 462), while with few rows the step is the weights' traffic and latency.
+// A warm call over 128 experts of 768 x 2048 (Q8_0), gate/up + down: 4096 tokens 555 +
+// 340 us with 128-row tiles and a weight row per staging lane, 462 + 309 us wide (890
+// TFLOP/s of gate/up MFMAs on real rows; a large library bf16 product: 1118); 61 tokens
+// 194 + 101 -> 116 + 62 us slim (3.5 TB/s of weights).
+// Each LDS stage is its own array, so that the compiler sees the reads of one stage not
+// alias the loads into the other.  The 1-D grid runs the column tiles of an M-tile, then
+// an expert's M-tiles, one after the other on the same XCD (block L runs on XCD L % 8), so
+// that their shared activation rows and weights come from that XCD's L2.
+constexpr int kWideThreads = 512, kSlimThreads = 256;
+template <int ROWS>
+using ActTile = __bf16[2][ROWS][64];  // [plane][row][k], 16-byte chunks swizzled by row
+typedef __bf16 WeightTile[256][kPfBK + 8];
+
+// A lane's raw bytes of one K step and weight row: a quarter g (16 weights) of the
+// step's 64.  Lane l loads quarter l % 4 of weight row l / 4, so that four
+// consecutive lanes read one row's 64 to 68 bytes: with the MFMA operands' own
+// order (row l % 16) every 16 lanes touch 16 rows and a load takes 64 cycles of
+// address work.  kDw: dwords; kLoads: the least number of load
+// instructions they take (16 bytes at most each); kAhead: steps ahead they are loaded.
+template <int FMT>
+struct WideRaw {
+  static constexpr int kDw = FMT == 8 ? 5 : FMT == 2 ? 5 : FMT == 12 ? 8 : 12;
+  static constexpr int kLoads = FMT == 8 ? 2 : FMT == 2 ? 2 : FMT == 12 ? 2 : 6;
+  static constexpr int kAhead = FMT == 14 || FMT == 12 ? 2 : 3;  // (K-quants: 32 and 48 registers per step)
+  static constexpr int kVector = FMT == 8 ? 210 : FMT == 2 ? 240 : FMT == 12 ? 260 : 290;  // vector instructions of a step
+};
+// K order of the steps.  A step multiplies 64 inputs; the sum over K does not
+// depend on the order in which they are visited, so a format may visit them in the
+// order its bytes hold them, as long as activations and weights use the same one.
+// Step kt, 16-byte chunk c of the activation tile's row (eight inputs) covers K
+// indices wide_kbase(kt) + wide_kchunk(c) + 0..7; quarter g of a weight row's step
+// meets chunks 2 g and 2 g + 1.
+// Q6_K: a step is one quarter (n, j) of a super-block, n = the half (128
+// weights), j = which 16 of each of its four 32-weight groups: the weights
+// 128 n + 32 g + 16 j + l (g < 4, l < 16), whose low bits sit in 16 bytes of
+// ql for g = 0, 2 (low and high nibbles), 16 bytes for g = 1, 3, and whose high
+// bits sit in 16 bytes of qh (two bits per group).  So every loaded byte is
+// used by one step only.
+template <int FMT>
+__device__ __forceinline__ uint32_t wide_kbase(int kt) {
+  if constexpr (FMT == 14) return 256u * (uint32_t)(kt >> 2) + 128u * (uint32_t)((kt >> 1) & 1) + 16u * (uint32_t)(kt & 1);
+  return (uint32_t)(kt * kPfBK);
+}
+template <int FMT>
+__device__ __forceinline__ uint32_t wide_kchunk(int c) {
+  if constexpr (FMT == 14) return 32u * (uint32_t)(c >> 1) + 8u * (uint32_t)(c & 1);
+  return 8u * (uint32_t)c;
+}
+// Every load stays inside the row's step (Q8_0, Q4_0, Q4_K) or, for Q6_K (210-byte
+// super-blocks, 2-byte aligned; a: the address rounded down to a dword), inside
+// [a, a + 212): a payload starts and ends 16-byte aligned, so its last super-block
+// starts at an address 2 mod 4 and ends at a + 212.
+template <int FMT>
+__device__ __forceinline__ void wide_load(const uint8_t *row, int kt, int g, uint32_t (&v)[WideRaw<FMT>::kDw]) {
+  auto x4 = [&](const uint8_t *p, int at) {
+    const u32x4 q = *(g_u32x4_a4 *)p;
+    v[at] = q.x;
+    v[at + 1] = q.y;
+    v[at + 2] = q.z;
+    v[at + 3] = q.w;
+  };
+  if constexpr (FMT == 8) {
+    // block g / 2 of the 68-byte pair: the five dwords around the 16 q bytes (its d is
+    // in the first dword of the even quarter)
+    const uint8_t *p = row + (int64_t)kt * 68 + 32 * (g >> 1);
+    x4(p + 16 * (g & 1), 0);
+    v[4] = *(const g_u32 *)(p + 16 * (g & 1) + 16);
+  } else if constexpr (FMT == 2) {
+    const uint8_t *p = row + (int64_t)kt * 36 + 16 * (g >> 1);
+    x4(p, 0);
+    v[4] = *(const g_u32 *)(p + 16);
+  } else if constexpr (FMT == 12) {
+    const uint8_t *b = row + (int64_t)(kt >> 2) * 144;
+    x4(b + 16 + 32 * (kt & 3) + 16 * (g & 1), 0);
+    x4(b, 4);
+  } else {
+    const uint8_t *b = row + (int64_t)(kt >> 2) * 210;
+    const uint8_t *a = b - ((uintptr_t)b & 3);
+    const int n = (kt >> 1) & 1, j = kt & 1;
+    const uint8_t *ql = a + 64 * n + 32 * (g & 1) + 16 * j, *qh = a + 128 + 32 * n + 16 * j;
+    x4(ql, 0);
+    v[4] = *(const g_u32 *)(ql + 16);
+    x4(qh, 5);
+    v[9] = *(const g_u32 *)(qh + 16);
+    v[10] = *(const g_u32 *)((uintptr_t)(b + 192 + 8 * n + 2 * g + j) & ~(uintptr_t)3);
+    v[11] = *(const g_u32 *)(a + 208);
+  }
+}
+// The quarter's 16 weights as bf16 (nearest even, from the fp32 value), eight per
+// MFMA operand.  Q8_0: d q.  Q4_0: the nibbles as signed bytes 16 (n - 8) (q4_lo /
+// q4_hi) times d / 16, both exact, so d (n - 8) rounded once.  Q4_K: d sc q - dmin m,
+// one fused multiply-add.  Q6_K: ds (q - 32) = fma(ds, q, -32 ds) (32 ds is exact).
+template <int FMT>
+__device__ __forceinline__ void wide_dequant(const uint32_t (&v)[WideRaw<FMT>::kDw], const uint8_t *row, int kt,
+                                             int g, bf16x8 (&o)[2]) {
+  if constexpr (FMT == 8 || FMT == 2) {
+    // block 0's q bytes start two bytes into the loaded dwords, block 1's one dword in
+    const bool b1 = g >> 1;
+    const uint32_t sel = b1 ? 0x07060504u : 0x05040302u;
+    // Q8_0: the first dword of the block, from the lane of its even quarter
+    const uint32_t dd = FMT == 8 ? (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v[0], 0xa0, 0xf, 0xf, false) : v[0];
+    const float d0 = half_bits_to_float(b1 ? dd >> 16 : dd & 0xffffu);
+    const float d = FMT == 8 ? d0 : 0.0625f * d0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      uint32_t w = __builtin_amdgcn_perm(v[j + 1], v[j], sel);
+      if constexpr (FMT == 2) w = ((w << ((g & 1) ? 0 : 4)) & 0xf0f0f0f0u) ^ 0x80808080u;
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+        o[j >> 1][4 * (j & 1) + b] = (__bf16)(d * (float)(int8_t)((w >> (8 * b)) & 0xffu));
+    }
+  } else if constexpr (FMT == 12) {
+    // sub-block 2 (kt % 4) + g / 2: low nibbles for g < 2, high for g >= 2
+    const uint32_t B0 = v[5], B1 = v[6], B2 = v[7];
+    const bool top = (kt & 3) >= 2;
+    const uint32_t SC = top ? ((B2 & 0x0f0f0f0fu) | ((B0 >> 2) & 0x30303030u)) : (B0 & 0x3f3f3f3fu);
+    const uint32_t MN = top ? (((B2 >> 4) & 0x0f0f0f0fu) | ((B1 >> 2) & 0x30303030u)) : (B1 & 0x3f3f3f3fu);
+    const int jj = 2 * (kt & 1) + (g >> 1);
+    const float d = half_bits_to_float(v[4] & 0xffffu), dmin = half_bits_to_float(v[4] >> 16);
+    const float ds = d * (float)((SC >> (8 * jj)) & 0xffu), dm = dmin * (float)((MN >> (8 * jj)) & 0xffu);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t q = (v[j] >> (4 * (g >> 1))) & 0x0f0f0f0fu;
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+        o[j >> 1][4 * (j & 1) + b] = (__bf16)fmaf(ds, (float)((q >> (8 * b)) & 0xffu), -dm);
+    }
+  } else {
+    // low four bits from the low (g < 2) or high nibbles, high two from bits 2 g, 2 g + 1 of qh
+    const uint8_t *bb = row + (int64_t)(kt >> 2) * 210;
+    const int sh = (int)((uintptr_t)bb & 3), n = (kt >> 1) & 1, j0 = kt & 1;
+    const int ss = (int)((uintptr_t)(bb + 192 + 8 * n + 2 * g + j0) & 3);
+    const float d = half_bits_to_float((v[11] >> (8 * sh)) & 0xffffu);
+    const float ds = d * (float)(int8_t)((v[10] >> (8 * ss)) & 0xffu), dm = -32.f * ds;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t lq = __builtin_amdgcn_alignbyte(v[j + 1], v[j], sh);
+      const uint32_t hq = __builtin_amdgcn_alignbyte(v[6 + j], v[5 + j], sh);
+      const uint32_t q = ((lq >> (4 * (g >> 1))) & 0x0f0f0f0fu) | (((hq >> (2 * g)) & 0x03030303u) << 4);
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+        o[j >> 1][4 * (j & 1) + b] = (__bf16)fmaf(ds, (float)((q >> (8 * b)) & 0xffu), dm);
+    }
+  }
+}
+
+// (slim kernels) Brings quarters held by lane 4 row + g to lane 16 g + row, the MFMA operand order.
+__device__ __forceinline__ void slim_permute(bf16x8 (&o)[2]) {
+  const int lane = threadIdx.x & (kWave - 1), src = 4 * (4 * (lane & 15) + (lane >> 4));
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    u32x4 d = __builtin_bit_cast(u32x4, o[h]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) d[i] = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)d[i]);
+    o[h] = __builtin_bit_cast(bf16x8, d);
+  }
+}
+
+// The (M-tile, column tile) of this block in the XCD-grouped order.
+__device__ __forceinline__ void wide_tile(int NT, int &mt, int &nt) {
+  const int total = gridDim.x, L = blockIdx.x, x = L % 8, idx = L / 8, per = total / 8, rem = total % 8;
+  const int w = x * per + min(x, rem) + idx;
+  mt = w / NT;
+  nt = w % NT;
+}
+
+// Waits until at most N vector memory operations of the wave are outstanding and its
+// LDS reads are done, then for the block.  (No fence: it would wait for every load in
+// flight.  What crosses the barrier is LDS written by direct loads, which the wait
+// covers, and stages read by finished LDS reads.)
+template <int N>
+__device__ __forceinline__ void wide_sync() {
+  static_assert(N < 64, "the wait counter has six bits");
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | ((N >> 4) << 14));  // vmcnt(N) lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// One tile of NI 16-row subtiles (KT >= 3 K steps): acc[i][q] = subtile i times the
+// wave's weight subtile q.  rows[q]: the row of weight subtile q that this lane loads; A: the
+// activation plane the wave loads from (wave wv: rows 16 u + 8 (wv / 2) .. +7 of
+// plane wv % 2); asrc(u): byte offset there of this lane's 16 bytes of subtile u.
+//
+// Order of a wave's vector memory operations in step kt: the direct loads of
+// kt + 2 (NI instructions), then the raw weights of kt + kAhead (at least LW).  At
+// the start of step kt the direct loads of kt have to be in: issued in step kt - 2,
+// they are followed by two steps' weights and one step's direct loads, so a wait
+// for at most 2 LW + NI outstanding operations covers them.  Three LDS stages rotate;
+// the loop's head runs KT % 3 steps so that the last three steps are a fixed tail.
+template <int FMT, int NI, class Src>
+__device__ __forceinline__ void slim_gemm(f32x4 (&acc)[NI][4], __amdgpu_buffer_rsrc_t A, Src asrc,
+                                          const uint8_t *const (&rows)[4], int KT, int wv, int lane, ActTile<kSlimBM> &As0,
+                                          ActTile<kSlimBM> &As1, ActTile<kSlimBM> &As2) {
+  constexpr int AH = WideRaw<FMT>::kAhead, LW = 4 * WideRaw<FMT>::kLoads;
+  const int g = lane >> 4;
+  uint32_t src[NI];
+#pragma unroll
+  for (int u = 0; u < NI; ++u) src[u] = asrc(u);
+  uint32_t W[3][4][WideRaw<FMT>::kDw];
+  bf16x8 bf[3][4][2];
+  auto aload = [&](int kt, ActTile<kSlimBM> &As) {
+#pragma unroll
+    for (int u = 0; u < NI; ++u)
+      dma16(A, src[u], 2 * wide_kbase<FMT>(kt), &As[wv & 1][16 * u + 8 * (wv >> 1)][0]);
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+  };
+  auto wload = [&](int kt, uint32_t (&w)[4][WideRaw<FMT>::kDw]) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) wide_load<FMT>(rows[q], kt, lane & 3, w[q]);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto dequant = [&](int kt, const uint32_t (&w)[4][WideRaw<FMT>::kDw], bf16x8 (&b)[4][2]) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      wide_dequant<FMT>(w[q], rows[q], kt, lane & 3, b[q]);
+      slim_permute(b[q]);
+    }
+  };
+  // A subtile's operands are read one subtile ahead of its eight MFMAs; the scheduling
+  // groups spread the step's dequantisation between the MFMAs (VMFMA of its vector
+  // instructions behind each), which leaves it in their shadow.
+  constexpr int VMFMA = (WideRaw<FMT>::kVector + 16 * NI - 1) / (16 * NI);
+  auto mma = [&](const ActTile<kSlimBM> &As, const bf16x8 (&b)[4][2]) {
+    bf16x8 hi[2], lo[2];
+    auto aread = [&](int s) {
+      const int r = 16 * (s % NI) + (lane & 15);
+      const int c = (2 * g + s / NI) ^ (r & 7);
+      hi[s & 1] = *reinterpret_cast<const bf16x8 *>(&As[0][r][8 * c]);
+      lo[s & 1] = *reinterpret_cast<const bf16x8 *>(&As[1][r][8 * c]);
+    };
+    aread(0);
+    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+#pragma unroll
+    for (int s = 0; s < 2 * NI; ++s) {
+      const int i = s % NI, ks = s / NI;
+      if (s + 1 < 2 * NI) {
+        aread(s + 1);
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        acc[i][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi[s & 1], b[q][ks], acc[i][q], 0, 0, 0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        acc[i][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo[s & 1], b[q][ks], acc[i][q], 0, 0, 0);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x2, VMFMA, 0);
+      }
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[i][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // step kt: operands bf[S], stage AC; bf[S1] takes kt + 1's weights from W[S1]; stage
+  // AN takes the activations of kt + 2; W[(S + AH) % 3] the raw weights of kt + AH
+#define SLIM_STEP(S, AC, AN, kt)                            \
+  do {                                                      \
+    wide_sync<2 * LW + NI>();                               \
+    aload((kt) + 2, AN);                                    \
+    wload((kt) + AH, W[((S) + AH) % 3]);                    \
+    dequant((kt) + 1, W[((S) + 1) % 3], bf[((S) + 1) % 3]); \
+    mma(AC, bf[S]);                                         \
+  } while (0)
+#define SLIM_HEAD(S, A0, A1)                                     \
+  do {                                                           \
+    wload(0, W[S]);                                              \
+    aload(0, A0);                                                \
+    wload(1, W[((S) + 1) % 3]);                                  \
+    aload(1, A1);                                                \
+    if constexpr (AH == 3) wload(2, W[((S) + 2) % 3]);           \
+    dequant(0, W[S], bf[S]);                                     \
+  } while (0)
+  const int lead = KT % 3;
+  int kt = 0;
+  // (a first step whose earlier operations are fewer than its wait allows would not
+  // wait for its own stage: the first two stages are waited for here)
+  if (lead == 0) {
+    SLIM_HEAD(0, As0, As1);
+  } else if (lead == 2) {
+    SLIM_HEAD(1, As1, As2);
+  } else {
+    SLIM_HEAD(2, As2, As0);
+  }
+  __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+  if (lead == 2) {
+    SLIM_STEP(1, As1, As0, 0);
+    kt = 1;
+  }
+  if (lead != 0) {
+    SLIM_STEP(2, As2, As1, kt);
+    ++kt;
+  }
+  for (; kt < KT - 3; kt += 3) {
+    SLIM_STEP(0, As0, As2, kt);
+    SLIM_STEP(1, As1, As0, kt + 1);
+    SLIM_STEP(2, As2, As1, kt + 2);
+  }
+  // the last three steps: nothing past the end is loaded
+  wide_sync<2 * LW + NI>();
+  aload(KT - 1, As2);
+  if constexpr (AH == 2) wload(KT - 1, W[2]);
+  dequant(KT - 2, W[1], bf[1]);
+  mma(As0, bf[0]);
+  wide_sync<AH == 2 ? 2 * LW + NI : LW + NI>();
+  dequant(KT - 1, W[2], bf[2]);
+  mma(As1, bf[1]);
+  wide_sync<0>();
+  mma(As2, bf[2]);
+#undef SLIM_STEP
+#undef SLIM_HEAD
+}
+
+// The wide kernels' producer waves: stage kt + 1 while the consumers multiply kt.
+// rows[q]: the weight rows this lane loads a quarter of (16 rows per q, 64 per wave);
+// asrc(u): as in slim_gemm.  At the end of a step the direct loads of kt + 1 have to be
+// in; the raw weights of kt + 2 (at least LW instructions, issued after them) may stay
+// in flight.
+template <int FMT, class Src>
+__device__ __forceinline__ void wide_produce(__amdgpu_buffer_rsrc_t A, Src asrc, int ni,
+                                             const uint8_t *const (&rows)[4], int KT, int pw, int lane,
+                                             ActTile<kWideBM> &As0, ActTile<kWideBM> &As1, WeightTile &Bs0,
+                                             WeightTile &Bs1) {
+  constexpr int LW = 4 * WideRaw<FMT>::kLoads, NU = kWideBM / 16;
+  const int g = lane & 3;
+  uint32_t src[NU];
+#pragma unroll
+  for (int u = 0; u < NU; ++u) src[u] = asrc(u);
+  uint32_t W0[4][WideRaw<FMT>::kDw], W1[4][WideRaw<FMT>::kDw];
+  auto aload = [&](int kt, ActTile<kWideBM> &As) {
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+      if (u < ni) dma16(A, src[u], 2 * wide_kbase<FMT>(kt), &As[pw & 1][16 * u + 8 * (pw >> 1)][0]);
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+  };
+  auto wload = [&](int kt, uint32_t (&w)[4][WideRaw<FMT>::kDw]) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) wide_load<FMT>(rows[q], kt, g, w[q]);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto stage = [&](int kt, const uint32_t (&w)[4][WideRaw<FMT>::kDw], WeightTile &Bs) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      bf16x8 o[2];
+      wide_dequant<FMT>(w[q], rows[q], kt, g, o);
+      __bf16 *dst = &Bs[64 * pw + 16 * q + (lane >> 2)][16 * g];
+      *reinterpret_cast<bf16x8 *>(dst) = o[0];
+      *reinterpret_cast<bf16x8 *>(dst + 8) = o[1];
+    }
+  };
+  aload(0, As0);
+  wload(0, W0);
+  wload(1, W1);
+  stage(0, W0, Bs0);
+  wide_sync<0>();
+  // step kt: the raw weights of kt + 1 are in WO, WS takes those of kt + 2
+#define WIDE_PROD(WS, WO, AN, BN, kt) \
+  do {                                \
+    aload((kt) + 1, AN);              \
+    wload((kt) + 2, WS);              \
+    stage((kt) + 1, WO, BN);          \
+    wide_sync<LW>();                  \
+  } while (0)
+  int kt = 0;
+  for (; kt + 4 <= KT; kt += 2) {  // both steps' loads are used by a later step
+    WIDE_PROD(W0, W1, As1, Bs1, kt);
+    WIDE_PROD(W1, W0, As0, Bs0, kt + 1);
+  }
+  // two or three steps are left: KT - kt
+  if (kt + 2 < KT) {
+    WIDE_PROD(W0, W1, As1, Bs1, kt);
+    aload(kt + 2, As0);
+    stage(kt + 2, W0, Bs0);
+  } else {
+    aload(kt + 1, As1);
+    stage(kt + 1, W1, Bs1);
+  }
+#undef WIDE_PROD
+  wide_sync<0>();
+  wide_sync<0>();
+}
+
+// The wide kernels' consumer waves: the K loop over a tile of NI subtiles.  brow[q]:
+// the tile's weight row where the wave's weight subtile q starts.
+template <int NI>
+__device__ __forceinline__ void wide_consume(f32x4 (&acc)[NI][4], int KT, const ActTile<kWideBM> &As0,
+                                             const ActTile<kWideBM> &As1, const WeightTile &Bs0,
+                                             const WeightTile &Bs1, const int (&brow)[4], int lane) {
+  auto mma = [&](const ActTile<kWideBM> &As, const WeightTile &Bs) {
+    bf16x8 hi[2], lo[2], bf[2][4];
+    auto aread = [&](int s) {
+      const int r = 16 * (s % NI) + (lane & 15);
+      const int c = (4 * (s / NI) + (lane >> 4)) ^ (r & 7);
+      hi[s & 1] = *reinterpret_cast<const bf16x8 *>(&As[0][r][8 * c]);
+      lo[s & 1] = *reinterpret_cast<const bf16x8 *>(&As[1][r][8 * c]);
+    };
+    auto bread = [&](int ks) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        bf[ks][q] = *reinterpret_cast<const bf16x8 *>(&Bs[brow[q] + (lane & 15)][32 * ks + 8 * (lane >> 4)]);
+    };
+    // every operand is read one subtile (eight MFMAs) before its use; without the
+    // scheduling groups the compiler reads some right before their MFMAs (1 to 3 %)
+    bread(0);
+    aread(0);
+    __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
+#pragma unroll
+    for (int s = 0; s < 2 * NI; ++s) {
+      const int i = s % NI;
+      if (s == NI - 1) {
+        bread(1);
+        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+      }
+      if (s + 1 < 2 * NI) {
+        aread(s + 1);
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x8, 8, 0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        acc[i][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi[s & 1], bf[s / NI][q], acc[i][q], 0, 0, 0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        acc[i][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo[s & 1], bf[s / NI][q], acc[i][q], 0, 0, 0);
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[i][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+  wide_sync<0>();
+  int kt = 0;
+  for (; kt + 2 <= KT; kt += 2) {
+    mma(As0, Bs0);
+    wide_sync<0>();
+    mma(As1, Bs1);
+    wide_sync<0>();
+  }
+  if (kt < KT) {
+    mma(As0, Bs0);
+    wide_sync<0>();
+  }
+}
+
+// A tile of ni subtiles runs the smallest instance that covers it (rows past the
+// tile's last are not stored).  MAX: the largest instance.
+template <int MAX, class F>
+__device__ __forceinline__ void wide_dispatch(int ni, F f) {
+  if constexpr (MAX > 4) {
+    if (ni > 8) return f(std::integral_constant<int, 9>{});
+    if (ni > 6) return f(std::integral_constant<int, 8>{});
+    if (ni > 4) return f(std::integral_constant<int, 6>{});
+  }
+  if (ni > 2) return f(std::integral_constant<int, 4>{});
+  if (ni > 1) return f(std::integral_constant<int, 2>{});
+  return f(std::integral_constant<int, 1>{});
+}
+
+// h = silu(g) u of the wave's 32 columns (acc[i][q] gate, acc[i][2 + q] up) as bf16 hi
+// and lo terms; out: the tile's first row at the lane's column.
+template <int NI>
+__device__ __forceinline__ void gateup_store(const f32x4 (&acc)[NI][4], __bf16 *out, int64_t lo_plane, int I, int n,
+                                             int lane) {
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = 16 * i + 4 * (lane >> 4) + r;
+      if (m < n) {
+        __bf16 *o = out + (int64_t)m * I;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const float v = silu_fast(acc[i][q][r]) * acc[i][2 + q][r];
+          const __bf16 hi = (__bf16)v;
+          o[16 * q] = hi;
+          o[lo_plane + 16 * q] = (__bf16)(v - (float)hi);
+        }
+      }
+    }
+}
+// P[pair] = w[pair] * row for the wave's 64 columns.
+template <int NI>
+__device__ __forceinline__ void down_store(const f32x4 (&acc)[NI][4], float *P, const int32_t *perm, const float *w,
+                                           int H, int n, int lane) {
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    int pair[4];
+    float wt[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) pair[r] = perm[min(16 * i + 4 * (lane >> 4) + r, n - 1)];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) wt[r] = w[pair[r]];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (16 * i + 4 * (lane >> 4) + r < n) {
+        float *dst = P + (int64_t)pair[r] * H;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) dst[16 * q] = wt[r] * acc[i][q][r];
+      }
+  }
+}
+
+// Gate/up (I a multiple of 128), wide: 128 columns of h per block, wave c's weight rows
+// are W_gate rows n0 + 32 c .. +31 and the same rows of W_up; h = silu(g) u written
+// as bf16 hi and lo terms at the pair's grouped row.
+template <int FMT>
+__global__ __launch_bounds__(kWideThreads, 1) void pf_gateup_wide_kernel(GmParams a) {
+  __shared__ __align__(16) ActTile<kWideBM> As0, As1;
+  __shared__ __align__(16) WeightTile Bs0, Bs1;
+  int mt, nt, j, m0;
+  wide_tile(a.I / 128, mt, nt);
+  if (!pf_tile(a.X, mt, j, m0)) return;
+  const int lane = threadIdx.x & (kWave - 1), wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), wv = wid & 3;
+  const int row0 = a.X.row0[j] + m0, n = min(a.X.n[j] - m0, (int)a.X.rt[j]), n0 = nt * 128 + 32 * wv;
+  const int32_t *perm = a.perm + row0;
+  const int H = a.H, I = a.I, k = a.k;
+  // the activation plane this wave loads (its bytes fit 32 bits, checked at launch)
+  const uint32_t plane = 2u * (uint32_t)a.T * (uint32_t)H;
+  const __amdgpu_buffer_rsrc_t A = wide_buffer(a.A + (wv & 1) * ((int64_t)a.T * H), plane);
+  auto asrc = [&](int u) {
+    const int r = min(16 * u + 8 * (wv >> 1) + (lane >> 3), n - 1);
+    return 2 * ((uint32_t)(perm[r] / k) * (uint32_t)H + wide_kchunk<FMT>((lane & 7) ^ (lane >> 3)));
+  };
+  const uint8_t *rows[4];  // producer wave c: rows 64 (c % 2) .. of W_gate (c < 2) or W_up
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    rows[q] = a.X.payload[j] + (wv >= 2 ? a.mat : 0) +
+              (int64_t)(nt * 128 + 64 * (wv & 1) + 16 * q + (lane >> 2)) * a.rowb;
+  if (wid >= 4) {
+    wide_produce<FMT>(A, asrc, (n + 15) / 16, rows, H / kPfBK, wv, lane, As0, As1, Bs0, Bs1);
+    return;
+  }
+  const int brow[4] = {32 * wv, 32 * wv + 16, 128 + 32 * wv, 128 + 32 * wv + 16};
+  __bf16 *out = a.ab + (int64_t)row0 * I + n0 + (lane & 15);
+  const int64_t lo_plane = (int64_t)a.pairs * I;
+  wide_dispatch<kWideBM / 16>((n + 15) / 16, [&](auto ni) {
+    constexpr int NI = decltype(ni)::value;
+    f32x4 acc[NI][4];
+    wide_consume<NI>(acc, H / kPfBK, As0, As1, Bs0, Bs1, brow, lane);
+    gateup_store<NI>(acc, out, lo_plane, I, n, lane);
+  });
+}
+
+// Down (H a multiple of 256), wide: wave c's weight rows are W_down rows n0 + 64 c .. +63;
+// the activation rows are the expert's, contiguous in perm order; P[pair] = w * row.
+template <int FMT>
+__global__ __launch_bounds__(kWideThreads, 1) void pf_down_wide_kernel(GmParams a) {
+  __shared__ __align__(16) ActTile<kWideBM> As0, As1;
+  __shared__ __align__(16) WeightTile Bs0, Bs1;
+  int mt, nt, j, m0;
+  wide_tile(a.H / 256, mt, nt);
+  if (!pf_tile(a.X, mt, j, m0)) return;
+  const int lane = threadIdx.x & (kWave - 1), wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), wv = wid & 3;
+  const int row0 = a.X.row0[j] + m0, n = min(a.X.n[j] - m0, (int)a.X.rt[j]), n0 = nt * 256 + 64 * wv;
+  const int32_t *perm = a.perm + row0;
+  const int H = a.H, I = a.I;
+  // the activation plane this wave loads (its bytes fit 32 bits, checked at launch)
+  const uint32_t plane = 2u * (uint32_t)a.pairs * (uint32_t)I;
+  const __amdgpu_buffer_rsrc_t A = wide_buffer(a.A + (wv & 1) * ((int64_t)a.pairs * I), plane);
+  auto asrc = [&](int u) {
+    const int r = min(16 * u + 8 * (wv >> 1) + (lane >> 3), n - 1);
+    return 2 * ((uint32_t)(row0 + r) * (uint32_t)I + wide_kchunk<FMT>((lane & 7) ^ (lane >> 3)));
+  };
+  const uint8_t *rows[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    rows[q] = a.X.payload[j] + a.down_off + (int64_t)(n0 + 16 * q + (lane >> 2)) * a.rowb;
+  if (wid >= 4) {
+    wide_produce<FMT>(A, asrc, (n + 15) / 16, rows, I / kPfBK, wv, lane, As0, As1, Bs0, Bs1);
+    return;
+  }
+  const int brow[4] = {64 * wv, 64 * wv + 16, 64 * wv + 32, 64 * wv + 48};
+  float *P = a.P + n0 + (lane & 15);
+  const float *w = a.w;
+  wide_dispatch<kWideBM / 16>((n + 15) / 16, [&](auto ni) {
+    constexpr int NI = decltype(ni)::value;
+    f32x4 acc[NI][4];
+    wide_consume<NI>(acc, I / kPfBK, As0, As1, Bs0, Bs1, brow, lane);
+    down_store<NI>(acc, P, perm, w, H, n, lane);
+  });
+}
+
+// Gate/up (I a multiple of 128), slim: 128 columns of h per block, wave c's weight rows
+// are W_gate rows n0 + 32 c .. +31 and the same rows of W_up; h = silu(g) u written
+// as bf16 hi and lo terms at the pair's grouped row.
+template <int FMT>
+__global__ __launch_bounds__(kSlimThreads, 2) void pf_gateup_slim_kernel(GmParams a) {
+  __shared__ __align__(16) ActTile<kSlimBM> As0, As1, As2;
+  int mt, nt, j, m0;
+  wide_tile(a.I / 128, mt, nt);
+  if (!pf_tile(a.X, mt, j, m0)) return;
+  const int lane = threadIdx.x & (kWave - 1), wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), wv = wid & 3;
+  const int row0 = a.X.row0[j] + m0, n = min(a.X.n[j] - m0, (int)a.X.rt[j]), n0 = nt * 128 + 32 * wv;
+  const int32_t *perm = a.perm + row0;
+  const int H = a.H, I = a.I, k = a.k;
+  // the activation plane this wave loads (its bytes fit 32 bits, checked at launch)
+  const uint32_t plane = 2u * (uint32_t)a.T * (uint32_t)H;
+  const __amdgpu_buffer_rsrc_t A = wide_buffer(a.A + (wv & 1) * ((int64_t)a.T * H), plane);
+  auto asrc = [&](int u) {
+    const int r = min(16 * u + 8 * (wv >> 1) + (lane >> 3), n - 1);
+    return 2 * ((uint32_t)(perm[r] / k) * (uint32_t)H + wide_kchunk<FMT>((lane & 7) ^ (lane >> 3)));
+  };
+  const uint8_t *rows[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    rows[q] = a.X.payload[j] + (q >= 2 ? a.mat : 0) + (int64_t)(n0 + 16 * (q & 1) + (lane >> 2)) * a.rowb;
+  __bf16 *out = a.ab + (int64_t)row0 * I + n0 + (lane & 15);
+  const int64_t lo_plane = (int64_t)a.pairs * I;
+  wide_dispatch<kSlimBM / 16>((n + 15) / 16, [&](auto ni) {
+    constexpr int NI = decltype(ni)::value;
+    f32x4 acc[NI][4];
+    slim_gemm<FMT, NI>(acc, A, asrc, rows, H / kPfBK, wv, lane, As0, As1, As2);
+    gateup_store<NI>(acc, out, lo_plane, I, n, lane);
+  });
+}
+
+// Down (H a multiple of 256), slim: wave c's weight rows are W_down rows n0 + 64 c .. +63;
+// the activation rows are the expert's, contiguous in perm order; P[pair] = w * row.
+template <int FMT>
+__global__ __launch_bounds__(kSlimThreads, 2) void pf_down_slim_kernel(GmParams a) {
+  __shared__ __align__(16) ActTile<kSlimBM> As0, As1, As2;
+  int mt, nt, j, m0;
+  wide_tile(a.H / 256, mt, nt);
+  if (!pf_tile(a.X, mt, j, m0)) return;
+  const int lane = threadIdx.x & (kWave - 1), wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), wv = wid & 3;
+  const int row0 = a.X.row0[j] + m0, n = min(a.X.n[j] - m0, (int)a.X.rt[j]), n0 = nt * 256 + 64 * wv;
+  const int32_t *perm = a.perm + row0;
+  const int H = a.H, I = a.I;
+  // the activation plane this wave loads (its bytes fit 32 bits, checked at launch)
+  const uint32_t plane = 2u * (uint32_t)a.pairs * (uint32_t)I;
+  const __amdgpu_buffer_rsrc_t A = wide_buffer(a.A + (wv & 1) * ((int64_t)a.pairs * I), plane);
+  auto asrc = [&](int u) {
+    const int r = min(16 * u + 8 * (wv >> 1) + (lane >> 3), n - 1);
+    return 2 * ((uint32_t)(row0 + r) * (uint32_t)I + wide_kchunk<FMT>((lane & 7) ^ (lane >> 3)));
+  };
+  const uint8_t *rows[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    rows[q] = a.X.payload[j] + a.down_off + (int64_t)(n0 + 16 * q + (lane >> 2)) * a.rowb;
+  float *P = a.P + n0 + (lane & 15);
+  const float *w = a.w;
+  wide_dispatch<kSlimBM / 16>((n + 15) / 16, [&](auto ni) {
+    constexpr int NI = decltype(ni)::value;
+    f32x4 acc[NI][4];
+    slim_gemm<FMT, NI>(acc, A, asrc, rows, I / kPfBK, wv, lane, As0, As1, As2);
+    down_store<NI>(acc, P, perm, w, H, n, lane);
+  });
+}
+
+}  // namespace
+
+template <int FMT>
+hipError_t wide_gateup(bool slim, dim3 grid, const GmParams &a, hipStream_t s, const Timing &t) {
+  if (slim)
+    hipExtLaunchKernelGGL(pf_gateup_slim_kernel<FMT>, grid, dim3(kSlimThreads), 0, s, t.start, t.stop, 0, a);
+  else
+    hipExtLaunchKernelGGL(pf_gateup_wide_kernel<FMT>, grid, dim3(kWideThreads), 0, s, t.start, t.stop, 0, a);
+  return hipGetLastError();
+}
+template <int FMT>
+hipError_t wide_down(bool slim, dim3 grid, const GmParams &a, hipStream_t s, const Timing &t) {
+  if (slim)
+    hipExtLaunchKernelGGL(pf_down_slim_kernel<FMT>, grid, dim3(kSlimThreads), 0, s, t.start, t.stop, 0, a);
+  else
+    hipExtLaunchKernelGGL(pf_down_wide_kernel<FMT>, grid, dim3(kWideThreads), 0, s, t.start, t.stop, 0, a);
+  return hipGetLastError();
+}
+
+}  // namespace moecache

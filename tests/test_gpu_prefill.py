@@ -190,6 +190,23 @@ def test_prefill_other_shapes(shape):
         run_prefill(wl, C, T)
 
 
+@pytest.mark.parametrize("qtype,shapes", [
+    ("q8_0", ((256, 192), (512, 384))), ("q4_0", ((768, 320), (256, 640))),
+    ("q4_k", ((256, 256), (512, 768))), ("q6_k", ((512, 768), (768, 512))),
+])
+def test_prefill_tile_edges(qtype, shapes):
+    """Rows per expert at the edges of the grouped GEMMs' tiles: with k = E every expert gets
+    all T tokens.  Subtiles of 16 rows and the instances that cover them (1, 2, 4, 6, 8, 9),
+    the last launch of 64-row tiles, one and two tiles of up to 144 rows; inner sizes of three
+    to twelve 64-wide steps, so every remainder of the loops' unrolling."""
+    for i, (hidden, inter) in enumerate(shapes):
+        wl = synth.WORKLOADS["tiny"].with_(name=f"edges_{qtype}_{hidden}_{inter}", qtype=qtype, n_experts=4,
+                                           top_k=4, hidden=hidden, inter=inter)
+        store = store_buffer(wl)
+        for T in ((9, 16, 33, 65, 144, 289), (17, 32, 64, 97, 129, 145, 288))[i]:
+            run_prefill(wl, 4, T, store=store, poison=True)
+
+
 def test_prefill_tiles_past_the_table():
     """A warm call whose 65 536 (token, expert) pairs make more 128-row tiles than the
     grouped GEMMs' per-launch tile table holds (512): the kernels find their tile by the

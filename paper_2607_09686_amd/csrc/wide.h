@@ -41,9 +41,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t wide_buffer(const void *p, uin
 //     Each wave loads and dequantises its own 64 weight rows into its MFMA operand
 //     registers (nothing of a weight goes through LDS), with the loads of later steps
 //     in flight and the activations two steps ahead in three LDS stages.
-// The line between them lies at 64 rows: a wave's vector instructions do not hide behind
-// its own MFMAs (one block of the slim kind per CU on 144-row tiles took 563 us where
-// wide takes 462), while with few rows the step is the weights' traffic and latency.
+// The line between them lies at 64 rows: whole warm calls of 12 to 120 tokens over 128
+// experts take 1 to 7 % less with slim tiles than with wide ones (Q4_0, 61 tokens: 211
+// us against 222; Q8_0: 244 against 250), 200 to 300 tokens the same within 3 %; above,
+// splitting experts into 64-row tiles loses (Q8_0, 1200 tokens: 442 us against 393), as
+// a wave's vector instructions do not hide behind its own MFMAs.
 // A warm call over 128 experts of 768 x 2048 (Q8_0), gate/up + down: 4096 tokens 555 +
 // 340 us with 128-row tiles and a weight row per staging lane, 462 + 309 us wide (890
 // TFLOP/s of gate/up MFMAs on real rows; a large library bf16 product: 1118); 61 tokens

@@ -41,6 +41,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t wide_buffer(const void *p, uin
 //     Each wave loads and dequantises its own 64 weight rows into its MFMA operand
 //     registers (nothing of a weight goes through LDS), with the loads of later steps
 //     in flight and the activations two steps ahead in three LDS stages.
+// Both multiply the same products in the same order into an accumulator, so that a row's
+// result does not depend on which of them, or which tile of it, computes the row.
 // The line between them lies at 64 rows: whole warm calls of 12 to 120 tokens over 128
 // experts take 1 to 7 % less with slim tiles than with wide ones (Q4_0, 61 tokens: 211
 // us against 222; Q8_0: 244 against 250), 200 to 300 tokens the same within 3 %; above,
@@ -192,16 +194,24 @@ __device__ __forceinline__ void wide_dequant(const uint32_t (&v)[WideRaw<FMT>::k
   }
 }
 
-// (slim kernels) Brings quarters held by lane 4 row + g to lane 16 g + row, the MFMA operand order.
+// (slim kernels) Brings the quarters of row r, held by lanes 4 r .. 4 r + 3, into the MFMA
+// operand order of the wide kernels: o[ks] of lane 16 g + r gets the eight weights that
+// meet chunk 4 ks + g, half g % 2 of quarter 2 ks + g / 2.  Lane group g fetches both
+// halves of quarter 0, 2, 1, 3; swapping the odd groups of the first halves with the
+// even groups of the second ones then leaves the chunks in order.
 __device__ __forceinline__ void slim_permute(bf16x8 (&o)[2]) {
-  const int lane = threadIdx.x & (kWave - 1), src = 4 * (4 * (lane & 15) + (lane >> 4));
+  const int lane = threadIdx.x & (kWave - 1), g = lane >> 4;
+  const int src = 4 * (4 * (lane & 15) + 2 * (g & 1) + (g >> 1));
+  u32x4 d[2] = {__builtin_bit_cast(u32x4, o[0]), __builtin_bit_cast(u32x4, o[1])};
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    u32x4 d = __builtin_bit_cast(u32x4, o[h]);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) d[i] = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)d[i]);
-    o[h] = __builtin_bit_cast(bf16x8, d);
+  for (int i = 0; i < 4; ++i) {
+    const auto r = __builtin_amdgcn_permlane16_swap((uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)d[0][i]),
+                                                    (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)d[1][i]), false, false);
+    d[0][i] = r[0];
+    d[1][i] = r[1];
   }
+  o[0] = __builtin_bit_cast(bf16x8, d[0]);
+  o[1] = __builtin_bit_cast(bf16x8, d[1]);
 }
 
 // The (M-tile, column tile) of this block in the XCD-grouped order.
@@ -277,7 +287,7 @@ __device__ __forceinline__ void slim_gemm(f32x4 (&acc)[NI][4], __amdgpu_buffer_r
     bf16x8 hi[2], lo[2];
     auto aread = [&](int s) {
       const int r = 16 * (s % NI) + (lane & 15);
-      const int c = (2 * g + s / NI) ^ (r & 7);
+      const int c = (4 * (s / NI) + g) ^ (r & 7);
       hi[s & 1] = *reinterpret_cast<const bf16x8 *>(&As[0][r][8 * c]);
       lo[s & 1] = *reinterpret_cast<const bf16x8 *>(&As[1][r][8 * c]);
     };

@@ -207,6 +207,35 @@ def test_prefill_tile_edges(qtype, shapes):
             run_prefill(wl, 4, T, store=store, poison=True)
 
 
+@pytest.mark.parametrize("qtype", ["q8_0", "q4_0", "q4_k", "q6_k", "q4_k_m"])
+def test_prefill_rows_same_in_every_launch(qtype):
+    """A row's result does not depend on the other experts of its launch: of eight experts some
+    have more than 64 rows (wide tiles) and some fewer (slim tiles where no expert of the launch
+    has more), and the launches are all eight at once (resident), two at a time (cold) and one at
+    a time (two slots).  The outputs of the three are equal bit for bit."""
+    torch = torch_cuda()
+    wl = synth.WORKLOADS["tiny"].with_(name=f"launches_{qtype}", qtype=qtype, n_experts=8, top_k=2, n_layers=1,
+                                       hidden=512, inter=768)
+    log(f"rows in every launch: {qtype} H={wl.hidden} I={wl.inter}")
+    keep, ptr, arr = store_buffer(wl)
+    R = synth.router(wl)[0]
+    X = synth.hidden(wl, rho=-1.0, n_tokens=250)
+    out = {}
+    for slots, calls in ((8, 2), (2, 1)):
+        cache = make_cache(wl, ptr, slots, prenorm=True)
+        for c in range(calls):
+            x = torch.from_numpy(X).cuda()
+            y = torch.empty_like(x)
+            _, idx, _ = cache.layer_forward(x, torch.from_numpy(R).cuda(), 0, y, n_tokens=len(X), routes=True)
+            torch.cuda.synchronize()
+            out[slots, c] = y.cpu().numpy()
+        cache.close()
+    rows = np.bincount(idx.ravel(), minlength=8)
+    assert rows.max() > 64 and (rows <= 64).sum() >= 3, rows
+    for key in ((8, 0), (2, 0)):
+        np.testing.assert_array_equal(out[key].view(np.uint32), out[8, 1].view(np.uint32), err_msg=str(key))
+
+
 def test_prefill_tiles_past_the_table():
     """A warm call whose 65 536 (token, expert) pairs make more 128-row tiles than the
     grouped GEMMs' per-launch tile table holds (512): the kernels find their tile by the

@@ -3889,8 +3889,11 @@ struct GmDown {
 };
 // The wide-tile kernels of a format.
 static hipError_t wide_launch(bool down, int fmt, dim3 g, const GmParams &a, hipStream_t s, const Timing &t) {
-  // the slim kernels where every tile of the launch has at most their 64 rows
-  bool slim = true;
+  // the slim kernels where every tile of the launch has at most their 64 rows; for Q6_K, whose
+  // dequantisation is the longest, the wide ones' separate staging waves are as fast at few
+  // rows and faster at many (12 to 61 tokens over 128 experts within 1.7 %, 250 tokens 311
+  // us a call against 324; Q4_K 257 us slim against 261 wide there, 219 against 228 at 61)
+  bool slim = fmt != 14;
   for (int i = 0; i < a.X.count; ++i) slim = slim && a.X.rt[i] <= kSlimBM;
   switch (fmt) {
     case 8: return down ? wide_down<8>(slim, g, a, s, t) : wide_gateup<8>(slim, g, a, s, t);

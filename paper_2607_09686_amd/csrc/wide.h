@@ -37,17 +37,19 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t wide_buffer(const void *p, uin
 //   wide (tiles of up to 144 rows): 512 threads, one block per CU.  Waves 0-3 multiply
 //     the current step, waves 4-7 stage the next one: the direct loads and the weight
 //     tile, dequantised into LDS.
-//   slim (launches whose tiles have at most 64 rows): 256 threads, two blocks per CU.
+//   slim (launches whose tiles have at most 64 rows, not Q6_K): 256 threads, two blocks per CU.
 //     Each wave loads and dequantises its own 64 weight rows into its MFMA operand
 //     registers (nothing of a weight goes through LDS), with the loads of later steps
 //     in flight and the activations two steps ahead in three LDS stages.
 // Both multiply the same products in the same order into an accumulator, so that a row's
 // result does not depend on which of them, or which tile of it, computes the row.
 // The line between them lies at 64 rows: whole warm calls of 12 to 120 tokens over 128
-// experts take 1 to 7 % less with slim tiles than with wide ones (Q4_0, 61 tokens: 211
-// us against 222; Q8_0: 244 against 250), 200 to 300 tokens the same within 3 %; above,
-// splitting experts into 64-row tiles loses (Q8_0, 1200 tokens: 442 us against 393), as
-// a wave's vector instructions do not hide behind its own MFMAs.
+// experts take 3 to 5 % less with slim tiles than with wide ones (61 tokens: Q4_0 213 us
+// against 221, Q8_0 243 against 255, Q4_K 219 against 228), 200 to 300 tokens the same
+// within 3 %; above, splitting experts into 64-row tiles loses (Q8_0, 1200 tokens: 442 us
+// against 393), as a wave's vector instructions do not hide behind its own MFMAs.  Q6_K has
+// no slim kernels: its dequantisation is the longest, and the wide kernels' staging waves are
+// as fast at few rows and faster at many (kernels.hip, wide_launch).
 // A warm call over 128 experts of 768 x 2048 (Q8_0), gate/up + down: 4096 tokens 555 +
 // 340 us with 128-row tiles and a weight row per staging lane, 462 + 309 us wide (890
 // TFLOP/s of gate/up MFMAs on real rows; a large library bf16 product: 1118); 61 tokens
@@ -61,19 +63,25 @@ template <int ROWS>
 using ActTile = __bf16[2][ROWS][64];  // [plane][row][k], 16-byte chunks swizzled by row
 typedef __bf16 WeightTile[256][kPfBK + 8];
 
-// A lane's raw bytes of one K step and weight row: a quarter g (16 weights) of the
-// step's 64.  Lane l loads quarter l % 4 of weight row l / 4, so that four
-// consecutive lanes read one row's 64 to 68 bytes: with the MFMA operands' own
-// order (row l % 16) every 16 lanes touch 16 rows and a load takes 64 cycles of
-// address work.  kDw: dwords; kLoads: the least number of load
-// instructions they take (16 bytes at most each); kAhead: steps ahead they are loaded.
-template <int FMT>
-struct WideRaw {
-  static constexpr int kDw = FMT == 8 ? 5 : FMT == 2 ? 5 : FMT == 12 ? 8 : 12;
-  static constexpr int kLoads = FMT == 8 ? 2 : FMT == 2 ? 2 : FMT == 12 ? 2 : 6;
-  static constexpr int kAhead = FMT == 14 || FMT == 12 ? 2 : 3;  // (K-quants: 32 and 48 registers per step)
-  static constexpr int kVector = FMT == 8 ? 210 : FMT == 2 ? 240 : FMT == 12 ? 260 : 290;  // vector instructions of a step
-};
+// A lane's raw bytes of one K step and weight row.  Lane l works on quarter g = l % 4 (16
+// weights) of weight row l / 4, so that four consecutive lanes read one row's 64 to 80
+// bytes: with the MFMA operands' own order (row l % 16) every 16 lanes touch 16 rows and a
+// load takes 64 cycles of address work.  Every format takes 20 bytes per lane, two load
+// instructions (16 + 4 bytes): what several quarters need of a K-quant's super-block, one
+// lane of the four loads and the others get by quad permutation.  (With each lane loading
+// all it needs, 12 dwords in six instructions for Q6_K and 8 in two for Q4_K, the slim kernels
+// spilled 312 to 357 and 8 to 10 registers; warm calls of 61 tokens over 128 experts took 376
+// us in Q6_K and 235 in Q4_K, now 288 and 217, and a Q4_K_M call of 4096 tokens 937, now 870.)
+constexpr int kRawDw = 5, kRawLoads = 2;
+typedef uint32_t RawStep[kRawDw];
+// Another lane's value of the four that share a row: quad_perm [C % 4, C / 4 % 4, ...].
+template <int C>
+__device__ __forceinline__ uint32_t quad(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, C, 0xf, 0xf, true);
+}
+// Keeps the compiler from masking and shifting each byte of q by itself: four bytes masked
+// at once, then one byte conversion each (80 of Q4_K's 395 vector instructions in a step).
+__device__ __forceinline__ void keep_bytes(uint32_t &q) { asm("" : "+v"(q)); }
 // K order of the steps.  A step multiplies 64 inputs; the sum over K does not
 // depend on the order in which they are visited, so a format may visit them in the
 // order its bytes hold them, as long as activations and weights use the same one.
@@ -96,59 +104,61 @@ __device__ __forceinline__ uint32_t wide_kchunk(int c) {
   if constexpr (FMT == 14) return 32u * (uint32_t)(c >> 1) + 8u * (uint32_t)(c & 1);
   return 8u * (uint32_t)c;
 }
-// Every load stays inside the row's step (Q8_0, Q4_0, Q4_K) or, for Q6_K (210-byte
-// super-blocks, 2-byte aligned; a: the address rounded down to a dword), inside
-// [a, a + 212): a payload starts and ends 16-byte aligned, so its last super-block
+// Every load stays inside the row's step (Q8_0, Q4_0), inside the super-block (Q4_K) or,
+// for Q6_K (210-byte super-blocks, 2-byte aligned; a: the address rounded down to a dword),
+// inside [a, a + 212): a payload starts and ends 16-byte aligned, so its last super-block
 // starts at an address 2 mod 4 and ends at a + 212.
+// base, off: see WeightRows.
 template <int FMT>
-__device__ __forceinline__ void wide_load(const uint8_t *row, int kt, int g, uint32_t (&v)[WideRaw<FMT>::kDw]) {
-  auto x4 = [&](const uint8_t *p, int at) {
-    const u32x4 q = *(g_u32x4_a4 *)p;
-    v[at] = q.x;
-    v[at + 1] = q.y;
-    v[at + 2] = q.z;
-    v[at + 3] = q.w;
-  };
+__device__ __forceinline__ void wide_load(const uint8_t *base, uint32_t off, int kt, int g, RawStep &v) {
+  uint32_t p, last;  // 16 bytes and the fifth dword
   if constexpr (FMT == 8) {
     // block g / 2 of the 68-byte pair: the five dwords around the 16 q bytes (its d is
     // in the first dword of the even quarter)
-    const uint8_t *p = row + (int64_t)kt * 68 + 32 * (g >> 1);
-    x4(p + 16 * (g & 1), 0);
-    v[4] = *(const g_u32 *)(p + 16 * (g & 1) + 16);
+    p = off + (uint32_t)kt * 68u + 16u * (uint32_t)g;
+    last = p + 16;
   } else if constexpr (FMT == 2) {
-    const uint8_t *p = row + (int64_t)kt * 36 + 16 * (g >> 1);
-    x4(p, 0);
-    v[4] = *(const g_u32 *)(p + 16);
+    p = off + (uint32_t)kt * 36u + 16u * (uint32_t)(g >> 1);
+    last = p + 16;
   } else if constexpr (FMT == 12) {
-    const uint8_t *b = row + (int64_t)(kt >> 2) * 144;
-    x4(b + 16 + 32 * (kt & 3) + 16 * (g & 1), 0);
-    x4(b, 4);
+    // the quarter's 16 q bytes; dword g of the super-block's header
+    const uint32_t b = off + (uint32_t)(kt >> 2) * 144u;
+    p = b + 16u + 32u * (uint32_t)(kt & 3) + 16u * (uint32_t)(g & 1);
+    last = b + 4u * (uint32_t)g;
   } else {
-    const uint8_t *b = row + (int64_t)(kt >> 2) * 210;
-    const uint8_t *a = b - ((uintptr_t)b & 3);
-    const int n = (kt >> 1) & 1, j = kt & 1;
-    const uint8_t *ql = a + 64 * n + 32 * (g & 1) + 16 * j, *qh = a + 128 + 32 * n + 16 * j;
-    x4(ql, 0);
-    v[4] = *(const g_u32 *)(ql + 16);
-    x4(qh, 5);
-    v[9] = *(const g_u32 *)(qh + 16);
-    v[10] = *(const g_u32 *)((uintptr_t)(b + 192 + 8 * n + 2 * g + j) & ~(uintptr_t)3);
-    v[11] = *(const g_u32 *)(a + 208);
+    // quarters 0 and 1: the 16 ql bytes of groups g and g + 2, at 64 n + 32 g + 16 j; 2: the
+    // 16 qh bytes of all groups, at 128 + 32 n + 16 j; 3: the super-block's 16 scales and d,
+    // at 192; with what lies before and behind them in the same dwords
+    const uint32_t n = (kt >> 1) & 1, j = kt & 1;
+    p = ((off + (uint32_t)(kt >> 2) * 210u) & ~3u) +
+        (((0xc0802000u + n * 0x00204040u + j * 0x00101010u) >> (8 * g)) & 0xffu);
+    last = p + 16;
   }
+  v[4] = *(const g_u32 *)(base + last);
+  // (the single dword of each row first: with all the 16-byte loads first a warm Q8_0 call of
+  // 61 tokens took 265 us instead of 243, with each row's 16 bytes first 253)
+  asm volatile("" ::: "memory");
+  const u32x4 q = *(g_u32x4_a4 *)(base + p);
+  v[0] = q.x;
+  v[1] = q.y;
+  v[2] = q.z;
+  v[3] = q.w;
+  asm volatile("" ::: "memory");
 }
 // The quarter's 16 weights as bf16 (nearest even, from the fp32 value), eight per
-// MFMA operand.  Q8_0: d q.  Q4_0: the nibbles as signed bytes 16 (n - 8) (q4_lo /
-// q4_hi) times d / 16, both exact, so d (n - 8) rounded once.  Q4_K: d sc q - dmin m,
-// one fused multiply-add.  Q6_K: ds (q - 32) = fma(ds, q, -32 ds) (32 ds is exact).
+// MFMA operand.  Q8_0: d q.  Q4_0: the nibbles as signed bytes 16 (n - 8) times d / 16,
+// both exact, so d (n - 8) rounded once.  Q4_K: d sc q - dmin m, one fused multiply-add.
+// Q6_K: ds (q - 32) = fma(ds, q, -32 ds) (32 ds is exact).
+// The choices that depend on kt (the same for every lane) are byte permutes and shifts: as
+// selects they become branches, which the scheduling groups of slim_gemm cannot cross.
 template <int FMT>
-__device__ __forceinline__ void wide_dequant(const uint32_t (&v)[WideRaw<FMT>::kDw], const uint8_t *row, int kt,
-                                             int g, bf16x8 (&o)[2]) {
+__device__ __forceinline__ void wide_dequant(const RawStep &v, uint32_t off, int kt, int g, bf16x8 (&o)[2]) {
   if constexpr (FMT == 8 || FMT == 2) {
     // block 0's q bytes start two bytes into the loaded dwords, block 1's one dword in
     const bool b1 = g >> 1;
     const uint32_t sel = b1 ? 0x07060504u : 0x05040302u;
     // Q8_0: the first dword of the block, from the lane of its even quarter
-    const uint32_t dd = FMT == 8 ? (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v[0], 0xa0, 0xf, 0xf, false) : v[0];
+    const uint32_t dd = FMT == 8 ? quad<0xa0>(v[0]) : v[0];
     const float d0 = half_bits_to_float(b1 ? dd >> 16 : dd & 0xffffu);
     const float d = FMT == 8 ? d0 : 0.0625f * d0;
 #pragma unroll
@@ -160,33 +170,44 @@ __device__ __forceinline__ void wide_dequant(const uint32_t (&v)[WideRaw<FMT>::k
         o[j >> 1][4 * (j & 1) + b] = (__bf16)(d * (float)(int8_t)((w >> (8 * b)) & 0xffu));
     }
   } else if constexpr (FMT == 12) {
-    // sub-block 2 (kt % 4) + g / 2: low nibbles for g < 2, high for g >= 2
-    const uint32_t B0 = v[5], B1 = v[6], B2 = v[7];
-    const bool top = (kt & 3) >= 2;
-    const uint32_t SC = top ? ((B2 & 0x0f0f0f0fu) | ((B0 >> 2) & 0x30303030u)) : (B0 & 0x3f3f3f3fu);
-    const uint32_t MN = top ? (((B2 >> 4) & 0x0f0f0f0fu) | ((B1 >> 2) & 0x30303030u)) : (B1 & 0x3f3f3f3fu);
-    const int jj = 2 * (kt & 1) + (g >> 1);
-    const float d = half_bits_to_float(v[4] & 0xffffu), dmin = half_bits_to_float(v[4] >> 16);
-    const float ds = d * (float)((SC >> (8 * jj)) & 0xffu), dm = dmin * (float)((MN >> (8 * jj)) & 0xffu);
+    // sub-block s = 2 (kt % 4) + g / 2 of the eight (low nibbles for g < 2, high for g >= 2);
+    // header: d and dmin, then the six-bit scales and mins of sub-blocks 0..3 in bytes s of B0
+    // and B1; of 4..7 the low four bits in byte s - 4 of B2, the high two in the upper bits of
+    // bytes s - 4 of B0 and B1
+    const uint32_t D = quad<0x00>(v[4]), B0 = quad<0x55>(v[4]), B1 = quad<0xaa>(v[4]), B2 = quad<0xff>(v[4]);
+    const int s = 2 * (kt & 3) + (g >> 1), up = 8 * (s & 3) + (kt & 2);
+    const uint32_t low = 0x0c0c0c00u | (uint32_t)s;  // byte s of eight, zero extended
+    const uint32_t sc = (__builtin_amdgcn_perm(B2, B0, low) & 0x0fu) | ((B0 >> up) & 0x30u);
+    const uint32_t mn = ((__builtin_amdgcn_perm(B2, B1, low) >> ((2 * kt) & 4)) & 0x0fu) | ((B1 >> up) & 0x30u);
+    const float d = half_bits_to_float(D & 0xffffu), dmin = half_bits_to_float(D >> 16);
+    const float ds = d * (float)sc, dm = dmin * (float)mn;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const uint32_t q = (v[j] >> (4 * (g >> 1))) & 0x0f0f0f0fu;
+      uint32_t q = (v[j] >> (4 * (g >> 1))) & 0x0f0f0f0fu;
+      keep_bytes(q);
 #pragma unroll
       for (int b = 0; b < 4; ++b)
         o[j >> 1][4 * (j & 1) + b] = (__bf16)fmaf(ds, (float)((q >> (8 * b)) & 0xffu), -dm);
     }
   } else {
-    // low four bits from the low (g < 2) or high nibbles, high two from bits 2 g, 2 g + 1 of qh
-    const uint8_t *bb = row + (int64_t)(kt >> 2) * 210;
-    const int sh = (int)((uintptr_t)bb & 3), n = (kt >> 1) & 1, j0 = kt & 1;
-    const int ss = (int)((uintptr_t)(bb + 192 + 8 * n + 2 * g + j0) & 3);
-    const float d = half_bits_to_float((v[11] >> (8 * sh)) & 0xffffu);
-    const float ds = d * (float)(int8_t)((v[10] >> (8 * ss)) & 0xffu), dm = -32.f * ds;
+    // the lane's own bytes at their place, then low four bits from the low (g < 2) or high
+    // nibbles of lane g % 2, high two from bits 2 g, 2 g + 1 of lane 2, scale 8 n + 2 g + j
+    // and d from lane 3
+    const int sh = (int)((off + 2u * (uint32_t)(kt >> 2)) & 3u), n = (kt >> 1) & 1, j0 = kt & 1;
+    uint32_t a[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) a[j] = __builtin_amdgcn_alignbyte(v[j + 1], v[j], sh);
+    const uint32_t half = n ? 0x07060504u : 0x03020100u;
+    const uint32_t s0 = quad<0xff>(__builtin_amdgcn_perm(a[2], a[0], half));
+    const uint32_t s1 = quad<0xff>(__builtin_amdgcn_perm(a[3], a[1], half));
+    const float d = half_bits_to_float(quad<0xff>(v[4] >> (8 * sh)) & 0xffffu);
+    const float ds = d * (float)(int8_t)__builtin_amdgcn_perm(s1, s0, 0x0c0c0c00u | (uint32_t)(2 * g + j0));
+    const float dm = -32.f * ds;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const uint32_t lq = __builtin_amdgcn_alignbyte(v[j + 1], v[j], sh);
-      const uint32_t hq = __builtin_amdgcn_alignbyte(v[6 + j], v[5 + j], sh);
-      const uint32_t q = ((lq >> (4 * (g >> 1))) & 0x0f0f0f0fu) | (((hq >> (2 * g)) & 0x03030303u) << 4);
+      const uint32_t lq = quad<0x44>(a[j]), hq = quad<0xaa>(a[j]);
+      uint32_t q = ((lq >> (4 * (g >> 1))) & 0x0f0f0f0fu) | (((hq >> (2 * g)) & 0x03030303u) << 4);
+      keep_bytes(q);
 #pragma unroll
       for (int b = 0; b < 4; ++b)
         o[j >> 1][4 * (j & 1) + b] = (__bf16)fmaf(ds, (float)((q >> (8 * b)) & 0xffu), dm);
@@ -194,24 +215,45 @@ __device__ __forceinline__ void wide_dequant(const uint32_t (&v)[WideRaw<FMT>::k
   }
 }
 
+// A wave's 64 weight rows as four subtiles of 16, two from `first` and two `second` bytes on:
+// base[q], the same for every lane, is the start of subtile q and off the distance from
+// there to the lane's row.  Payloads are 16-byte aligned and 16 rows of any format a
+// multiple of four bytes, so every base is dword aligned.  (A pointer per lane and subtile
+// took eight registers and a 64-bit sum for each load.)
+struct WeightRows {
+  const uint8_t *base[4];
+  uint32_t off;
+  __device__ __forceinline__ WeightRows(const uint8_t *first, int64_t rowb, int64_t second, int lane)
+      : base{first, first + 16 * rowb, first + second, first + second + 16 * rowb},
+        off((uint32_t)(lane >> 2) * (uint32_t)rowb) {}
+};
+
 // (slim kernels) Brings the quarters of row r, held by lanes 4 r .. 4 r + 3, into the MFMA
 // operand order of the wide kernels: o[ks] of lane 16 g + r gets the eight weights that
 // meet chunk 4 ks + g, half g % 2 of quarter 2 ks + g / 2.  Lane group g fetches both
 // halves of quarter 0, 2, 1, 3; swapping the odd groups of the first halves with the
 // even groups of the second ones then leaves the chunks in order.
-__device__ __forceinline__ void slim_permute(bf16x8 (&o)[2]) {
+__device__ __forceinline__ void slim_fetch(bf16x8 (&o)[2]) {
   const int lane = threadIdx.x & (kWave - 1), g = lane >> 4;
   const int src = 4 * (4 * (lane & 15) + 2 * (g & 1) + (g >> 1));
-  u32x4 d[2] = {__builtin_bit_cast(u32x4, o[0]), __builtin_bit_cast(u32x4, o[1])};
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    u32x4 d = __builtin_bit_cast(u32x4, o[h]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) d[i] = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)d[i]);
+    o[h] = __builtin_bit_cast(bf16x8, d);
+  }
+}
+__device__ __forceinline__ void slim_swap(bf16x8 (&o)[2]) {
+  u32x4 d0 = __builtin_bit_cast(u32x4, o[0]), d1 = __builtin_bit_cast(u32x4, o[1]);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const auto r = __builtin_amdgcn_permlane16_swap((uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)d[0][i]),
-                                                    (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)d[1][i]), false, false);
-    d[0][i] = r[0];
-    d[1][i] = r[1];
+    const auto r = __builtin_amdgcn_permlane16_swap(d0[i], d1[i], false, false);
+    d0[i] = r[0];
+    d1[i] = r[1];
   }
-  o[0] = __builtin_bit_cast(bf16x8, d[0]);
-  o[1] = __builtin_bit_cast(bf16x8, d[1]);
+  o[0] = __builtin_bit_cast(bf16x8, d0);
+  o[1] = __builtin_bit_cast(bf16x8, d1);
 }
 
 // The (M-tile, column tile) of this block in the XCD-grouped order.
@@ -238,26 +280,26 @@ __device__ __forceinline__ void wide_sync() {
 }
 
 // One tile of NI 16-row subtiles (KT >= 3 K steps): acc[i][q] = subtile i times the
-// wave's weight subtile q.  rows[q]: the row of weight subtile q that this lane loads; A: the
+// wave's weight subtile q.  base[q], off: where the row of weight subtile q that this lane loads starts; A: the
 // activation plane the wave loads from (wave wv: rows 16 u + 8 (wv / 2) .. +7 of
 // plane wv % 2); asrc(u): byte offset there of this lane's 16 bytes of subtile u.
 //
 // Order of a wave's vector memory operations in step kt: the direct loads of
-// kt + 2 (NI instructions), then the raw weights of kt + kAhead (at least LW).  At
+// kt + 2 (NI instructions), then the raw weights of kt + 3 (at least LW).  At
 // the start of step kt the direct loads of kt have to be in: issued in step kt - 2,
 // they are followed by two steps' weights and one step's direct loads, so a wait
 // for at most 2 LW + NI outstanding operations covers them.  Three LDS stages rotate;
 // the loop's head runs KT % 3 steps so that the last three steps are a fixed tail.
 template <int FMT, int NI, class Src>
 __device__ __forceinline__ void slim_gemm(f32x4 (&acc)[NI][4], __amdgpu_buffer_rsrc_t A, Src asrc,
-                                          const uint8_t *const (&rows)[4], int KT, int wv, int lane, ActTile<kSlimBM> &As0,
-                                          ActTile<kSlimBM> &As1, ActTile<kSlimBM> &As2) {
-  constexpr int AH = WideRaw<FMT>::kAhead, LW = 4 * WideRaw<FMT>::kLoads;
+                                          const uint8_t *const (&base)[4], uint32_t off, int KT, int wv, int lane,
+                                          ActTile<kSlimBM> &As0, ActTile<kSlimBM> &As1, ActTile<kSlimBM> &As2) {
+  constexpr int LW = 4 * kRawLoads;
   const int g = lane >> 4;
   uint32_t src[NI];
 #pragma unroll
   for (int u = 0; u < NI; ++u) src[u] = asrc(u);
-  uint32_t W[3][4][WideRaw<FMT>::kDw];
+  RawStep W[3][4];
   bf16x8 bf[3][4][2];
   auto aload = [&](int kt, ActTile<kSlimBM> &As) {
 #pragma unroll
@@ -266,23 +308,25 @@ __device__ __forceinline__ void slim_gemm(f32x4 (&acc)[NI][4], __amdgpu_buffer_r
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("" ::: "memory");
   };
-  auto wload = [&](int kt, uint32_t (&w)[4][WideRaw<FMT>::kDw]) {
+  auto wload = [&](int kt, RawStep (&w)[4]) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) wide_load<FMT>(rows[q], kt, lane & 3, w[q]);
-    asm volatile("" ::: "memory");
+    for (int q = 0; q < 4; ++q) wide_load<FMT>(base[q], off, kt, lane & 3, w[q]);
     __builtin_amdgcn_sched_barrier(0);
   };
-  auto dequant = [&](int kt, const uint32_t (&w)[4][WideRaw<FMT>::kDw], bf16x8 (&b)[4][2]) {
+  auto dequant = [&](int kt, const RawStep (&w)[4], bf16x8 (&b)[4][2]) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      wide_dequant<FMT>(w[q], rows[q], kt, lane & 3, b[q]);
-      slim_permute(b[q]);
+      wide_dequant<FMT>(w[q], off, kt, lane & 3, b[q]);
+      slim_fetch(b[q]);
+      if (q > 0) slim_swap(b[q - 1]);  // (its fetches have come back by now)
     }
+    slim_swap(b[3]);
   };
   // A subtile's operands are read one subtile ahead of its eight MFMAs; the scheduling
   // groups spread the step's dequantisation between the MFMAs (VMFMA of its vector
   // instructions behind each), which leaves it in their shadow.
-  constexpr int VMFMA = (WideRaw<FMT>::kVector + 16 * NI - 1) / (16 * NI);
+  constexpr int kVector = FMT == 8 ? 210 : FMT == 2 ? 240 : 320;  // vector instructions of a step
+  constexpr int VMFMA = (kVector + 16 * NI - 1) / (16 * NI);
   auto mma = [&](const ActTile<kSlimBM> &As, const bf16x8 (&b)[4][2]) {
     bf16x8 hi[2], lo[2];
     auto aread = [&](int s) {
@@ -318,12 +362,12 @@ __device__ __forceinline__ void slim_gemm(f32x4 (&acc)[NI][4], __amdgpu_buffer_r
 #pragma unroll
     for (int q = 0; q < 4; ++q) acc[i][q] = f32x4{0.f, 0.f, 0.f, 0.f};
   // step kt: operands bf[S], stage AC; bf[S1] takes kt + 1's weights from W[S1]; stage
-  // AN takes the activations of kt + 2; W[(S + AH) % 3] the raw weights of kt + AH
+  // AN takes the activations of kt + 2; W[S] the raw weights of kt + 3
 #define SLIM_STEP(S, AC, AN, kt)                            \
   do {                                                      \
     wide_sync<2 * LW + NI>();                               \
     aload((kt) + 2, AN);                                    \
-    wload((kt) + AH, W[((S) + AH) % 3]);                    \
+    wload((kt) + 3, W[S]);                                  \
     dequant((kt) + 1, W[((S) + 1) % 3], bf[((S) + 1) % 3]); \
     mma(AC, bf[S]);                                         \
   } while (0)
@@ -333,7 +377,7 @@ __device__ __forceinline__ void slim_gemm(f32x4 (&acc)[NI][4], __amdgpu_buffer_r
     aload(0, A0);                                                \
     wload(1, W[((S) + 1) % 3]);                                  \
     aload(1, A1);                                                \
-    if constexpr (AH == 3) wload(2, W[((S) + 2) % 3]);           \
+    wload(2, W[((S) + 2) % 3]);                                  \
     dequant(0, W[S], bf[S]);                                     \
   } while (0)
   const int lead = KT % 3;
@@ -364,10 +408,9 @@ __device__ __forceinline__ void slim_gemm(f32x4 (&acc)[NI][4], __amdgpu_buffer_r
   // the last three steps: nothing past the end is loaded
   wide_sync<2 * LW + NI>();
   aload(KT - 1, As2);
-  if constexpr (AH == 2) wload(KT - 1, W[2]);
   dequant(KT - 2, W[1], bf[1]);
   mma(As0, bf[0]);
-  wide_sync<AH == 2 ? 2 * LW + NI : LW + NI>();
+  wide_sync<LW + NI>();
   dequant(KT - 1, W[2], bf[2]);
   mma(As1, bf[1]);
   wide_sync<0>();
@@ -377,21 +420,20 @@ __device__ __forceinline__ void slim_gemm(f32x4 (&acc)[NI][4], __amdgpu_buffer_r
 }
 
 // The wide kernels' producer waves: stage kt + 1 while the consumers multiply kt.
-// rows[q]: the weight rows this lane loads a quarter of (16 rows per q, 64 per wave);
-// asrc(u): as in slim_gemm.  At the end of a step the direct loads of kt + 1 have to be
+// base, off: the weight rows this lane loads a quarter of; asrc(u): as in slim_gemm.  At the end of a step the direct loads of kt + 1 have to be
 // in; the raw weights of kt + 2 (at least LW instructions, issued after them) may stay
 // in flight.
 template <int FMT, class Src>
 __device__ __forceinline__ void wide_produce(__amdgpu_buffer_rsrc_t A, Src asrc, int ni,
-                                             const uint8_t *const (&rows)[4], int KT, int pw, int lane,
+                                             const uint8_t *const (&base)[4], uint32_t off, int KT, int pw, int lane,
                                              ActTile<kWideBM> &As0, ActTile<kWideBM> &As1, WeightTile &Bs0,
                                              WeightTile &Bs1) {
-  constexpr int LW = 4 * WideRaw<FMT>::kLoads, NU = kWideBM / 16;
+  constexpr int LW = 4 * kRawLoads, NU = kWideBM / 16;
   const int g = lane & 3;
   uint32_t src[NU];
 #pragma unroll
   for (int u = 0; u < NU; ++u) src[u] = asrc(u);
-  uint32_t W0[4][WideRaw<FMT>::kDw], W1[4][WideRaw<FMT>::kDw];
+  RawStep W0[4], W1[4];
   auto aload = [&](int kt, ActTile<kWideBM> &As) {
 #pragma unroll
     for (int u = 0; u < NU; ++u)
@@ -399,17 +441,16 @@ __device__ __forceinline__ void wide_produce(__amdgpu_buffer_rsrc_t A, Src asrc,
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("" ::: "memory");
   };
-  auto wload = [&](int kt, uint32_t (&w)[4][WideRaw<FMT>::kDw]) {
+  auto wload = [&](int kt, RawStep (&w)[4]) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) wide_load<FMT>(rows[q], kt, g, w[q]);
-    asm volatile("" ::: "memory");
+    for (int q = 0; q < 4; ++q) wide_load<FMT>(base[q], off, kt, g, w[q]);
     __builtin_amdgcn_sched_barrier(0);
   };
-  auto stage = [&](int kt, const uint32_t (&w)[4][WideRaw<FMT>::kDw], WeightTile &Bs) {
+  auto stage = [&](int kt, const RawStep (&w)[4], WeightTile &Bs) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       bf16x8 o[2];
-      wide_dequant<FMT>(w[q], rows[q], kt, g, o);
+      wide_dequant<FMT>(w[q], off, kt, g, o);
       __bf16 *dst = &Bs[64 * pw + 16 * q + (lane >> 2)][16 * g];
       *reinterpret_cast<bf16x8 *>(dst) = o[0];
       *reinterpret_cast<bf16x8 *>(dst + 8) = o[1];
@@ -545,7 +586,8 @@ __device__ __forceinline__ void gateup_store(const f32x4 (&acc)[NI][4], __bf16 *
       }
     }
 }
-// P[pair] = w[pair] * row for the wave's 64 columns.
+// P[pair] = w[pair] * row for the wave's 64 columns, the first of them at P.  (The lane's
+// column is added here: a pointer kept through the K loop cost the slim kernels spills.)
 template <int NI>
 __device__ __forceinline__ void down_store(const f32x4 (&acc)[NI][4], float *P, const int32_t *perm, const float *w,
                                            int H, int n, int lane) {
@@ -560,7 +602,7 @@ __device__ __forceinline__ void down_store(const f32x4 (&acc)[NI][4], float *P, 
 #pragma unroll
     for (int r = 0; r < 4; ++r)
       if (16 * i + 4 * (lane >> 4) + r < n) {
-        float *dst = P + (int64_t)pair[r] * H;
+        float *dst = P + (int64_t)pair[r] * H + (lane & 15);
 #pragma unroll
         for (int q = 0; q < 4; ++q) dst[16 * q] = wt[r] * acc[i][q][r];
       }
@@ -588,13 +630,11 @@ __global__ __launch_bounds__(kWideThreads, 1) void pf_gateup_wide_kernel(GmParam
     const int r = min(16 * u + 8 * (wv >> 1) + (lane >> 3), n - 1);
     return 2 * ((uint32_t)(perm[r] / k) * (uint32_t)H + wide_kchunk<FMT>((lane & 7) ^ (lane >> 3)));
   };
-  const uint8_t *rows[4];  // producer wave c: rows 64 (c % 2) .. of W_gate (c < 2) or W_up
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-    rows[q] = a.X.payload[j] + (wv >= 2 ? a.mat : 0) +
-              (int64_t)(nt * 128 + 64 * (wv & 1) + 16 * q + (lane >> 2)) * a.rowb;
+  // producer wave c: rows 64 (c % 2) .. of W_gate (c < 2) or W_up
+  const WeightRows W(a.X.payload[j] + (wv >= 2 ? a.mat : 0) + (int64_t)(nt * 128 + 64 * (wv & 1)) * a.rowb, a.rowb,
+                     32 * a.rowb, lane);
   if (wid >= 4) {
-    wide_produce<FMT>(A, asrc, (n + 15) / 16, rows, H / kPfBK, wv, lane, As0, As1, Bs0, Bs1);
+    wide_produce<FMT>(A, asrc, (n + 15) / 16, W.base, W.off, H / kPfBK, wv, lane, As0, As1, Bs0, Bs1);
     return;
   }
   const int brow[4] = {32 * wv, 32 * wv + 16, 128 + 32 * wv, 128 + 32 * wv + 16};
@@ -628,16 +668,13 @@ __global__ __launch_bounds__(kWideThreads, 1) void pf_down_wide_kernel(GmParams 
     const int r = min(16 * u + 8 * (wv >> 1) + (lane >> 3), n - 1);
     return 2 * ((uint32_t)(row0 + r) * (uint32_t)I + wide_kchunk<FMT>((lane & 7) ^ (lane >> 3)));
   };
-  const uint8_t *rows[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-    rows[q] = a.X.payload[j] + a.down_off + (int64_t)(n0 + 16 * q + (lane >> 2)) * a.rowb;
+  const WeightRows W(a.X.payload[j] + a.down_off + (int64_t)n0 * a.rowb, a.rowb, 32 * a.rowb, lane);
   if (wid >= 4) {
-    wide_produce<FMT>(A, asrc, (n + 15) / 16, rows, I / kPfBK, wv, lane, As0, As1, Bs0, Bs1);
+    wide_produce<FMT>(A, asrc, (n + 15) / 16, W.base, W.off, I / kPfBK, wv, lane, As0, As1, Bs0, Bs1);
     return;
   }
   const int brow[4] = {64 * wv, 64 * wv + 16, 64 * wv + 32, 64 * wv + 48};
-  float *P = a.P + n0 + (lane & 15);
+  float *P = a.P + n0;
   const float *w = a.w;
   wide_dispatch<kWideBM / 16>((n + 15) / 16, [&](auto ni) {
     constexpr int NI = decltype(ni)::value;
@@ -667,16 +704,13 @@ __global__ __launch_bounds__(kSlimThreads, 2) void pf_gateup_slim_kernel(GmParam
     const int r = min(16 * u + 8 * (wv >> 1) + (lane >> 3), n - 1);
     return 2 * ((uint32_t)(perm[r] / k) * (uint32_t)H + wide_kchunk<FMT>((lane & 7) ^ (lane >> 3)));
   };
-  const uint8_t *rows[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-    rows[q] = a.X.payload[j] + (q >= 2 ? a.mat : 0) + (int64_t)(n0 + 16 * (q & 1) + (lane >> 2)) * a.rowb;
+  const WeightRows W(a.X.payload[j] + (int64_t)n0 * a.rowb, a.rowb, a.mat, lane);
   __bf16 *out = a.ab + (int64_t)row0 * I + n0 + (lane & 15);
   const int64_t lo_plane = (int64_t)a.pairs * I;
   wide_dispatch<kSlimBM / 16>((n + 15) / 16, [&](auto ni) {
     constexpr int NI = decltype(ni)::value;
     f32x4 acc[NI][4];
-    slim_gemm<FMT, NI>(acc, A, asrc, rows, H / kPfBK, wv, lane, As0, As1, As2);
+    slim_gemm<FMT, NI>(acc, A, asrc, W.base, W.off, H / kPfBK, wv, lane, As0, As1, As2);
     gateup_store<NI>(acc, out, lo_plane, I, n, lane);
   });
 }
@@ -700,36 +734,38 @@ __global__ __launch_bounds__(kSlimThreads, 2) void pf_down_slim_kernel(GmParams 
     const int r = min(16 * u + 8 * (wv >> 1) + (lane >> 3), n - 1);
     return 2 * ((uint32_t)(row0 + r) * (uint32_t)I + wide_kchunk<FMT>((lane & 7) ^ (lane >> 3)));
   };
-  const uint8_t *rows[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-    rows[q] = a.X.payload[j] + a.down_off + (int64_t)(n0 + 16 * q + (lane >> 2)) * a.rowb;
-  float *P = a.P + n0 + (lane & 15);
+  const WeightRows W(a.X.payload[j] + a.down_off + (int64_t)n0 * a.rowb, a.rowb, 32 * a.rowb, lane);
+  float *P = a.P + n0;
   const float *w = a.w;
   wide_dispatch<kSlimBM / 16>((n + 15) / 16, [&](auto ni) {
     constexpr int NI = decltype(ni)::value;
     f32x4 acc[NI][4];
-    slim_gemm<FMT, NI>(acc, A, asrc, rows, I / kPfBK, wv, lane, As0, As1, As2);
+    slim_gemm<FMT, NI>(acc, A, asrc, W.base, W.off, I / kPfBK, wv, lane, As0, As1, As2);
     down_store<NI>(acc, P, perm, w, H, n, lane);
   });
 }
 
 }  // namespace
 
+// The slim kernels take Q8_0, Q4_0 and Q4_K.
 template <int FMT>
 hipError_t wide_gateup(bool slim, dim3 grid, const GmParams &a, hipStream_t s, const Timing &t) {
-  if (slim)
-    hipExtLaunchKernelGGL(pf_gateup_slim_kernel<FMT>, grid, dim3(kSlimThreads), 0, s, t.start, t.stop, 0, a);
-  else
-    hipExtLaunchKernelGGL(pf_gateup_wide_kernel<FMT>, grid, dim3(kWideThreads), 0, s, t.start, t.stop, 0, a);
+  if constexpr (FMT != 14)
+    if (slim) {
+      hipExtLaunchKernelGGL(pf_gateup_slim_kernel<FMT>, grid, dim3(kSlimThreads), 0, s, t.start, t.stop, 0, a);
+      return hipGetLastError();
+    }
+  hipExtLaunchKernelGGL(pf_gateup_wide_kernel<FMT>, grid, dim3(kWideThreads), 0, s, t.start, t.stop, 0, a);
   return hipGetLastError();
 }
 template <int FMT>
 hipError_t wide_down(bool slim, dim3 grid, const GmParams &a, hipStream_t s, const Timing &t) {
-  if (slim)
-    hipExtLaunchKernelGGL(pf_down_slim_kernel<FMT>, grid, dim3(kSlimThreads), 0, s, t.start, t.stop, 0, a);
-  else
-    hipExtLaunchKernelGGL(pf_down_wide_kernel<FMT>, grid, dim3(kWideThreads), 0, s, t.start, t.stop, 0, a);
+  if constexpr (FMT != 14)
+    if (slim) {
+      hipExtLaunchKernelGGL(pf_down_slim_kernel<FMT>, grid, dim3(kSlimThreads), 0, s, t.start, t.stop, 0, a);
+      return hipGetLastError();
+    }
+  hipExtLaunchKernelGGL(pf_down_wide_kernel<FMT>, grid, dim3(kWideThreads), 0, s, t.start, t.stop, 0, a);
   return hipGetLastError();
 }
 

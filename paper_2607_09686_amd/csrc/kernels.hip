@@ -3889,11 +3889,12 @@ struct GmDown {
 };
 // The wide-tile kernels of a format.
 static hipError_t wide_launch(bool down, int fmt, dim3 g, const GmParams &a, hipStream_t s, const Timing &t) {
-  // the slim kernels where every tile of the launch has at most their 64 rows; for Q6_K, whose
+  // the slim kernels where every tile of the launch has at most their 64 rows and the sum
+  // over K the three steps that they hold in flight; for Q6_K, whose
   // dequantisation is the longest, the wide ones' separate staging waves are as fast at few
   // rows and faster at many (12 to 61 tokens over 128 experts within 1.7 %, 250 tokens 311
   // us a call against 324; Q4_K 257 us slim against 261 wide there, 219 against 228 at 61)
-  bool slim = fmt != 14;
+  bool slim = fmt != 14 && (down ? a.I : a.H) >= 3 * kPfBK;
   for (int i = 0; i < a.X.count; ++i) slim = slim && a.X.rt[i] <= kSlimBM;
   switch (fmt) {
     case 8: return down ? wide_down<8>(slim, g, a, s, t) : wide_gateup<8>(slim, g, a, s, t);
@@ -3910,7 +3911,7 @@ hipError_t launch_pf_gateup(int qtype, const PfWave &W, const int32_t *perm, con
   GmParams a{};
   const int fmt = fmt_gate_up(qtype);
   // wide tiles, every format: element offsets into both activation planes have to fit 32 bits
-  const bool wide = I % 128 == 0 && H % 64 == 0 && H >= 3 * kPfBK && 2 * (int64_t)T * H <= (int64_t)UINT32_MAX;
+  const bool wide = I % 128 == 0 && H % 64 == 0 && 2 * (int64_t)T * H <= (int64_t)UINT32_MAX;
   const int tiles = gm_experts(W, wide ? kWideBM : kPfBM, a.X);
   a.perm = perm;
   a.A = xb;
@@ -3956,7 +3957,7 @@ hipError_t launch_pf_down(int qtype, const PfWave &W, const int32_t *perm, const
   GmParams a{};
   const int fmt = fmt_down(qtype);
   // wide tiles, every format: element offsets into both activation planes have to fit 32 bits
-  const bool wide = H % 256 == 0 && I % 64 == 0 && I >= 3 * kPfBK && 2 * (int64_t)pairs * I <= (int64_t)UINT32_MAX;
+  const bool wide = H % 256 == 0 && I % 64 == 0 && 2 * (int64_t)pairs * I <= (int64_t)UINT32_MAX;
   const int tiles = gm_experts(W, wide ? kWideBM : kPfBM, a.X);
   a.perm = perm;
   a.A = ab;

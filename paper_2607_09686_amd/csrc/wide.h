@@ -37,7 +37,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t wide_buffer(const void *p, uin
 //   wide (tiles of up to 144 rows): 512 threads, one block per CU.  Waves 0-3 multiply
 //     the current step, waves 4-7 stage the next one: the direct loads and the weight
 //     tile, dequantised into LDS.
-//   slim (launches whose tiles have at most 64 rows, not Q6_K): 256 threads, two blocks per CU.
+//   slim (launches whose tiles have at most 64 rows, at least three K steps, not Q6_K): 256
+//     threads, two blocks per CU.
 //     Each wave loads and dequantises its own 64 weight rows into its MFMA operand
 //     registers (nothing of a weight goes through LDS), with the loads of later steps
 //     in flight and the activations two steps ahead in three LDS stages.
@@ -458,9 +459,13 @@ __device__ __forceinline__ void wide_produce(__amdgpu_buffer_rsrc_t A, Src asrc,
   };
   aload(0, As0);
   wload(0, W0);
-  wload(1, W1);
+  if (KT > 1) wload(1, W1);
   stage(0, W0, Bs0);
   wide_sync<0>();
+  if (KT == 1) {
+    wide_sync<0>();  // (the consumers' only step)
+    return;
+  }
   // step kt: the raw weights of kt + 1 are in WO, WS takes those of kt + 2
 #define WIDE_PROD(WS, WO, AN, BN, kt) \
   do {                                \

@@ -190,20 +190,36 @@ def test_prefill_other_shapes(shape):
         run_prefill(wl, C, T)
 
 
-@pytest.mark.parametrize("qtype,shapes", [
-    ("q8_0", ((256, 192), (512, 384))), ("q4_0", ((768, 320), (256, 640))),
-    ("q4_k", ((256, 256), (512, 768))), ("q6_k", ((512, 768), (768, 512))),
-])
-def test_prefill_tile_edges(qtype, shapes):
+# (gate/up takes the wide-tile kernels where inter is a multiple of 128, down where hidden is one
+# of 256; a K-quant's sizes are multiples of 256)
+@pytest.mark.parametrize("qtype,hidden,inter", [("q8_0", 512, 384), ("q4_0", 768, 640),
+                                                ("q4_k", 512, 768), ("q6_k", 768, 512)])
+def test_prefill_tile_edges(qtype, hidden, inter):
     """Rows per expert at the edges of the grouped GEMMs' tiles: with k = E every expert gets
     all T tokens.  Subtiles of 16 rows and the instances that cover them (1, 2, 4, 6, 8, 9),
-    the last launch of 64-row tiles, one and two tiles of up to 144 rows; inner sizes of three
-    to twelve 64-wide steps, so every remainder of the loops' unrolling."""
-    for i, (hidden, inter) in enumerate(shapes):
-        wl = synth.WORKLOADS["tiny"].with_(name=f"edges_{qtype}_{hidden}_{inter}", qtype=qtype, n_experts=4,
+    the last launch of 64-row tiles, one and two tiles of up to 144 rows, in gate/up and down."""
+    wl = synth.WORKLOADS["tiny"].with_(name=f"edges_{qtype}", qtype=qtype, n_experts=4, top_k=4,
+                                       hidden=hidden, inter=inter)
+    store = store_buffer(wl)
+    for T in (9, 16, 17, 32, 33, 64, 65, 96, 97, 128, 129, 144, 145, 288, 289):
+        run_prefill(wl, 4, T, store=store, poison=True)
+
+
+@pytest.mark.parametrize("qtype,shapes", [
+    # gate/up sums of one to five 64-wide K steps; down sums of one, three, five; both of two ...
+    ("q8_0", ((64, 256), (128, 384), (192, 256), (320, 384), (256, 64), (256, 192), (256, 320), (256, 128))),
+    ("q4_0", ((64, 384), (128, 256), (192, 384), (320, 256), (256, 64), (256, 192), (256, 320), (256, 128))),
+    ("q4_k", ((256, 256), (256, 512), (512, 256))), ("q6_k", ((256, 256), (256, 512), (512, 256))),
+])
+def test_prefill_inner_sizes(qtype, shapes):
+    """Short sums over K, every remainder of the loops' unrolling, in launches of 64-row tiles
+    and of larger ones: one and two steps, where the wide-tile kernels' staging waves have
+    nothing or one step to run ahead, and three, the least that the slim kernels take."""
+    for hidden, inter in shapes:
+        wl = synth.WORKLOADS["tiny"].with_(name=f"inner_{qtype}_{hidden}_{inter}", qtype=qtype, n_experts=4,
                                            top_k=4, hidden=hidden, inter=inter)
         store = store_buffer(wl)
-        for T in ((9, 16, 33, 65, 144, 289), (17, 32, 64, 97, 129, 145, 288))[i]:
+        for T in (17, 100, 289):
             run_prefill(wl, 4, T, store=store, poison=True)
 
 

@@ -591,25 +591,26 @@ __device__ __forceinline__ void gateup_store(const f32x4 (&acc)[NI][4], __bf16 *
       }
     }
 }
-// P[pair] = w[pair] * row for the wave's 64 columns, the first of them at P.  (The lane's
-// column is added here: a pointer kept through the K loop cost the slim kernels spills.)
-template <int NI>
-__device__ __forceinline__ void down_store(const f32x4 (&acc)[NI][4], float *P, const int32_t *perm, const float *w,
-                                           int H, int n, int lane) {
+// P[pair] = w[pair] * row for the wave's 64 columns, the first of them at P; row(m): the pair of
+// tile row m and its weight.  (The lane's column is added here: a pointer kept through the K
+// loop cost the slim kernels spills.)
+struct RowPair {
+  int32_t pair;
+  float w;
+};
+template <int NI, class Row>
+__device__ __forceinline__ void down_store(const f32x4 (&acc)[NI][4], float *P, Row row, int H, int n, int lane) {
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
-    int pair[4];
-    float wt[4];
+    RowPair rp[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) pair[r] = perm[min(16 * i + 4 * (lane >> 4) + r, n - 1)];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) wt[r] = w[pair[r]];
+    for (int r = 0; r < 4; ++r) rp[r] = row(min(16 * i + 4 * (lane >> 4) + r, n - 1));
 #pragma unroll
     for (int r = 0; r < 4; ++r)
       if (16 * i + 4 * (lane >> 4) + r < n) {
-        float *dst = P + (int64_t)pair[r] * H + (lane & 15);
+        float *dst = P + (int64_t)rp[r].pair * H + (lane & 15);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) dst[16 * q] = wt[r] * acc[i][q][r];
+        for (int q = 0; q < 4; ++q) dst[16 * q] = rp[r].w * acc[i][q][r];
       }
   }
 }
@@ -659,6 +660,7 @@ template <int FMT>
 __global__ __launch_bounds__(kWideThreads, 1) void pf_down_wide_kernel(GmParams a) {
   __shared__ __align__(16) ActTile<kWideBM> As0, As1;
   __shared__ __align__(16) WeightTile Bs0, Bs1;
+  __shared__ RowPair rows[kWideBM];
   int mt, nt, j, m0;
   wide_tile(a.H / 256, mt, nt);
   if (!pf_tile(a.X, mt, j, m0)) return;
@@ -678,14 +680,19 @@ __global__ __launch_bounds__(kWideThreads, 1) void pf_down_wide_kernel(GmParams 
     wide_produce<FMT>(A, asrc, (n + 15) / 16, W.base, W.off, I / kPfBK, wv, lane, As0, As1, Bs0, Bs1);
     return;
   }
+  // the rows' pairs and weights, while the first step is staged: loaded in the epilogue, each
+  // subtile's two dependent loads made it the longest part of a tile of one or two K steps
+  if ((int)threadIdx.x < n) {
+    const int pair = perm[threadIdx.x];
+    rows[threadIdx.x] = {pair, a.w[pair]};
+  }
   const int brow[4] = {64 * wv, 64 * wv + 16, 64 * wv + 32, 64 * wv + 48};
   float *P = a.P + n0;
-  const float *w = a.w;
   wide_dispatch<kWideBM / 16>((n + 15) / 16, [&](auto ni) {
     constexpr int NI = decltype(ni)::value;
     f32x4 acc[NI][4];
     wide_consume<NI>(acc, I / kPfBK, As0, As1, Bs0, Bs1, brow, lane);
-    down_store<NI>(acc, P, perm, w, H, n, lane);
+    down_store<NI>(acc, P, [&](int m) { return rows[m]; }, H, n, lane);
   });
 }
 
@@ -746,7 +753,7 @@ __global__ __launch_bounds__(kSlimThreads, 2) void pf_down_slim_kernel(GmParams 
     constexpr int NI = decltype(ni)::value;
     f32x4 acc[NI][4];
     slim_gemm<FMT, NI>(acc, A, asrc, W.base, W.off, I / kPfBK, wv, lane, As0, As1, As2);
-    down_store<NI>(acc, P, perm, w, H, n, lane);
+    down_store<NI>(acc, P, [&](int m) { return RowPair{perm[m], w[perm[m]]}; }, H, n, lane);
   });
 }
 

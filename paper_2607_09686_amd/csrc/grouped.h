@@ -44,9 +44,10 @@ typedef __attribute__((address_space(1))) const uint32_t g_u32;
 __device__ __forceinline__ uint32_t q4_lo(uint32_t w) { return ((w << 4) & 0xf0f0f0f0u) ^ 0x80808080u; }
 __device__ __forceinline__ uint32_t q4_hi(uint32_t w) { return (w & 0xf0f0f0f0u) ^ 0x80808080u; }
 
-// One wave's experts for the grouped GEMMs (kernel argument, about 3 KB).
+// One wave's experts for the grouped GEMMs (kernel argument, 3.3 KB; all arguments of a
+// launch together have to stay within 4 KB).
 constexpr int kPfMaxExperts = 128;
-constexpr int kPfMaxTiles = 448;  // (arguments stay within 4 KB)
+constexpr int kPfMaxTiles = 512;  // 128 experts of up to 576 rows in tiles of 144
 struct PfExperts {
   const uint8_t *payload[kPfMaxExperts];
   int32_t row0[kPfMaxExperts];  // first row of the expert's pairs in perm / Ab

@@ -253,14 +253,17 @@ def test_prefill_rows_same_in_every_launch(qtype):
 
 
 def test_prefill_tiles_past_the_table():
-    """A warm call whose 65 536 (token, expert) pairs make more 128-row tiles than the
-    grouped GEMMs' per-launch tile table holds (512): the kernels find their tile by the
-    scan over the experts instead.  The first call copies every expert in; the second
-    runs all 16 as hits in one launch.  Routes, trace, counters and every token's
-    output against the bf16-weight oracle."""
+    """A warm call whose 98 304 (token, expert) pairs make about 700 tiles of at most 144 rows,
+    more than the grouped GEMMs' per-launch tile table holds (512): the kernels, gate/up and
+    down both with wide tiles, find their tile by the scan over the experts instead.  The
+    first call copies every expert in; the second runs all 16 as hits in one launch.  Routes,
+    trace, counters and every token's output against the bf16-weight oracle."""
+    T, E, k = 12288, 16, 8
+    assert T * k // 144 > 1.3 * 512
     for qt in ("q8_0", "q4_0"):
-        wl = synth.WORKLOADS["tiny"].with_(n_experts=16, top_k=8, qtype=qt, name=f"pftiles_{qt}")
-        run_prefill(wl, 16, 8192, calls=2)
+        wl = synth.WORKLOADS["tiny"].with_(n_experts=E, top_k=k, qtype=qt, name=f"pftiles_{qt}")
+        assert wl.inter % 128 == 0 and wl.hidden % 256 == 0
+        run_prefill(wl, E, T, calls=2)
 
 
 @pytest.mark.parametrize("name,budget,calls", [("a3b_prefill", None, 1), ("q4km_prefill", None, 1),

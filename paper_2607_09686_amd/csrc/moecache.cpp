@@ -86,10 +86,11 @@ struct moe_cache {
   float *xsc = nullptr;         //   and their block scales [H/32]
   int32_t *topk_idx = nullptr;  // device [cap_tokens][k]
   float *topk_w = nullptr;
-  float *zbuf = nullptr;  // prefill logits [cap_tokens][E]
   int64_t cap_tokens = 0;
-  // prefill buffers (grown on demand)
+  // prefill buffers (one allocation, grown on demand)
+  uint8_t *pf_buf = nullptr;
   int64_t pf_cap = 0;
+  float *pf_z = nullptr;        // partial logits, router_zbuf_floats(T, E)
   float *pf_inv = nullptr;      // [T]
   __bf16 *pf_xb = nullptr;      // [2][T][H] (hi, lo)
   int32_t *pf_counts = nullptr; // grouping scratch, group_counts_ints(E)
@@ -282,17 +283,10 @@ void free_all(moe_cache *c) {
   (void)hipFree(c->partial);
   (void)hipFree(c->topk_idx);
   (void)hipFree(c->topk_w);
-  (void)hipFree(c->zbuf);
   (void)hipFree(c->hq);
   (void)hipFree(c->hsc);
   (void)hipFree(c->hds);
-  (void)hipFree(c->pf_inv);
-  (void)hipFree(c->pf_xb);
-  (void)hipFree(c->pf_counts);
-  (void)hipFree(c->pf_off);
-  (void)hipFree(c->pf_perm);
-  (void)hipFree(c->pf_ab);
-  (void)hipFree(c->pf_P);
+  (void)hipFree(c->pf_buf);
   if (c->pf_host_off) (void)hipHostFree(c->pf_host_off);
   if (c->st_host_idx) (void)hipHostFree(c->st_host_idx);
   (void)hipFree(c->st_xq);
@@ -339,15 +333,12 @@ int ensure_tokens(moe_cache *c, int64_t T) {
   HIP_TRY(c, hipStreamSynchronize(c->main));
   (void)hipFree(c->topk_idx);
   (void)hipFree(c->topk_w);
-  (void)hipFree(c->zbuf);
   c->topk_idx = nullptr;
   c->topk_w = nullptr;
-  c->zbuf = nullptr;
   c->cap_tokens = 0;
-  const int64_t k = c->d.top_k, E = c->d.n_experts;
+  const int64_t k = c->d.top_k;
   if (hipMalloc(&c->topk_idx, T * k * sizeof(int32_t)) != hipSuccess ||
-      hipMalloc(&c->topk_w, T * k * sizeof(float)) != hipSuccess ||
-      hipMalloc(&c->zbuf, router_zbuf_floats(T, (int)E) * sizeof(float)) != hipSuccess)
+      hipMalloc(&c->topk_w, T * k * sizeof(float)) != hipSuccess)
     return fail(MOE_ENOMEM, "cannot allocate routing buffers for %lld tokens", (long long)T);
   c->cap_tokens = T;
   return MOE_OK;
@@ -1360,30 +1351,41 @@ int moe_probe_hbm_read(uint64_t bytes, int32_t iters, double *read_us, double *e
 
 namespace {
 
+// The buffers lie in one allocation: a first long call grows them all, and a free and an
+// allocation take 50 to 800 us each, whatever their size (from 640 to 4096 tokens of A3B
+// shape, as eight buffers and the partial logits' ninth: 1.1 to 1.4 ms before the call's 0.85).
 int ensure_prefill(moe_cache *c, int64_t T) {
   if (T <= c->pf_cap) return MOE_OK;
   HIP_TRY(c, hipStreamSynchronize(c->main));
-  void *ptrs[] = {c->pf_inv, c->pf_xb, c->pf_counts, c->pf_off, c->pf_perm, c->pf_ab, c->pf_P};
-  for (void *q : ptrs) (void)hipFree(q);
-  c->pf_inv = nullptr;
-  c->pf_xb = nullptr;
-  c->pf_counts = c->pf_off = c->pf_perm = nullptr;
-  c->pf_ab = nullptr;
-  c->pf_P = nullptr;
+  (void)hipFree(c->pf_buf);
+  c->pf_buf = nullptr;
   c->pf_cap = 0;
   const int64_t H = c->d.hidden, I = c->d.inter, E = c->d.n_experts, k = c->d.top_k;
-  if (hipMalloc(&c->pf_inv, T * sizeof(float)) != hipSuccess ||
-      hipMalloc(&c->pf_xb, 2 * T * H * sizeof(__bf16)) != hipSuccess ||
-      hipMalloc(&c->pf_counts, group_counts_ints((int)E) * sizeof(int32_t)) != hipSuccess ||
-      hipMalloc(&c->pf_off, (E + 1) * sizeof(int32_t)) != hipSuccess ||
-      hipMalloc(&c->pf_perm, T * k * sizeof(int32_t)) != hipSuccess ||
-      hipMalloc(&c->pf_ab, 2 * T * k * I * sizeof(__bf16)) != hipSuccess ||
-      hipMalloc(&c->pf_P, T * k * H * sizeof(float)) != hipSuccess ||
+  int64_t total = 0;
+  auto place = [&](int64_t bytes) {
+    const int64_t at = total;
+    total += (bytes + 255) / 256 * 256;
+    return at;
+  };
+  const int64_t z = place(router_zbuf_floats(T, (int)E) * sizeof(float));
+  const int64_t inv = place(T * sizeof(float)), xb = place(2 * T * H * sizeof(__bf16));
+  const int64_t counts = place(group_counts_ints((int)E) * sizeof(int32_t));
+  const int64_t off = place((E + 1) * sizeof(int32_t)), perm = place(T * k * sizeof(int32_t));
+  const int64_t ab = place(2 * T * k * I * sizeof(__bf16)), P = place(T * k * H * sizeof(float));
+  if (hipMalloc(&c->pf_buf, total) != hipSuccess ||
       (!c->pf_host_off &&
        hipHostMalloc(&c->pf_host_off, 257 * sizeof(int32_t), hipHostMallocDefault) != hipSuccess)) {
     (void)hipGetLastError();
     return fail(MOE_ENOMEM, "cannot allocate prefill buffers for %lld tokens", (long long)T);
   }
+  c->pf_z = reinterpret_cast<float *>(c->pf_buf + z);
+  c->pf_inv = reinterpret_cast<float *>(c->pf_buf + inv);
+  c->pf_xb = reinterpret_cast<__bf16 *>(c->pf_buf + xb);
+  c->pf_counts = reinterpret_cast<int32_t *>(c->pf_buf + counts);
+  c->pf_off = reinterpret_cast<int32_t *>(c->pf_buf + off);
+  c->pf_perm = reinterpret_cast<int32_t *>(c->pf_buf + perm);
+  c->pf_ab = reinterpret_cast<__bf16 *>(c->pf_buf + ab);
+  c->pf_P = reinterpret_cast<float *>(c->pf_buf + P);
   c->pf_cap = T;
   return MOE_OK;
 }
@@ -1516,7 +1518,7 @@ int forward_prefill_impl(moe_cache *c, const float *x, int32_t T, const float *w
             2ull * T * H * E);
     sp.record_start();
     HIP_TRY(c, launch_prefill_prep(x, T, H, prenorm, c->pf_inv, c->pf_xb, c->main));
-    HIP_TRY(c, launch_router_prefill(x, wr, T, H, E, k, prenorm ? c->pf_inv : nullptr, c->zbuf,
+    HIP_TRY(c, launch_router_prefill(x, wr, T, H, E, k, prenorm ? c->pf_inv : nullptr, c->pf_z,
                                      c->topk_idx, c->topk_w, c->main));
     HIP_TRY(c, launch_group(c->topk_idx, T * k, E, c->pf_counts, c->pf_off, c->pf_perm, c->main));
     sp.record_stop();

@@ -252,6 +252,31 @@ def test_prefill_rows_same_in_every_launch(qtype):
         np.testing.assert_array_equal(out[key].view(np.uint32), out[8, 1].view(np.uint32), err_msg=str(key))
 
 
+def test_prefill_buffers_regrown():
+    """The multi-token buffers of a handle grow with its longest call: shorter and longer calls in
+    turn (the partial logits' slices change with the length) give the outputs, bit for bit, of a
+    fresh handle each."""
+    torch = torch_cuda()
+    wl = synth.WORKLOADS["tiny"].with_(n_layers=1, hidden=512, inter=384, name="regrown")
+    keep, ptr, arr = store_buffer(wl)
+    r = torch.from_numpy(synth.router(wl)[0]).cuda()
+
+    def call(cache, T):
+        x = torch.from_numpy(synth.hidden(wl.with_(hidden_seed=wl.hidden_seed + T), rho=-1.0, n_tokens=T)).cuda()
+        y = torch.empty_like(x)
+        cache.layer_forward(x, r, 0, y, n_tokens=T)
+        torch.cuda.synchronize()
+        return y.cpu().numpy()
+
+    one = make_cache(wl, ptr, wl.n_experts, residual=True, prenorm=True)
+    for T in (20, 300, 33, 1100, 1, 257, 2100, 9):
+        log(f"regrown: T={T}")
+        fresh = make_cache(wl, ptr, wl.n_experts, residual=True, prenorm=True)
+        np.testing.assert_array_equal(call(one, T).view(np.uint32), call(fresh, T).view(np.uint32))
+        fresh.close()
+    one.close()
+
+
 def test_prefill_tiles_past_the_table():
     """A warm call whose 98 304 (token, expert) pairs make about 700 tiles of at most 144 rows,
     more than the grouped GEMMs' per-launch tile table holds (512): the kernels, gate/up and

@@ -36,14 +36,6 @@ typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
 typedef __attribute__((address_space(1))) const u32x4_a4 g_u32x4_a4;
 typedef __attribute__((address_space(1))) const uint32_t g_u32;
 
-// Four Q4_0 nibbles of a dword as signed bytes 16 (n - 8): bit 3 of the nibble
-// flipped makes it the 4-bit two's complement of n - 8, and at the top of its
-// byte (the other nibble cleared) the byte is 16 (n - 8).  q4_lo takes the low
-// nibble of each byte, q4_hi the high one; the flip of bit 7 after the shift
-// is the flip of bit 3 before it.
-__device__ __forceinline__ uint32_t q4_lo(uint32_t w) { return ((w << 4) & 0xf0f0f0f0u) ^ 0x80808080u; }
-__device__ __forceinline__ uint32_t q4_hi(uint32_t w) { return (w & 0xf0f0f0f0u) ^ 0x80808080u; }
-
 // One wave's experts for the grouped GEMMs (kernel argument, 3.3 KB; all arguments of a
 // launch together have to stay within 4 KB).
 constexpr int kPfMaxExperts = 128;

@@ -1119,6 +1119,14 @@ __device__ __forceinline__ float recombine(int i1, int i2, int i3) {
   return fmaf((float)i3, 1.f / 64516.f, fmaf((float)i2, 1.f / 254.f, (float)i1));
 }
 
+// Four Q4_0 nibbles of a dword as signed bytes 16 (n - 8): bit 3 of the nibble
+// flipped makes it the 4-bit two's complement of n - 8, and at the top of its
+// byte (the other nibble cleared) the byte is 16 (n - 8).  q4_lo takes the low
+// nibble of each byte, q4_hi the high one; the flip of bit 7 after the shift
+// is the flip of bit 3 before it.
+__device__ __forceinline__ uint32_t q4_lo(uint32_t w) { return ((w << 4) & 0xf0f0f0f0u) ^ 0x80808080u; }
+__device__ __forceinline__ uint32_t q4_hi(uint32_t w) { return (w & 0xf0f0f0f0u) ^ 0x80808080u; }
+
 // Partial dot of one pair with the inputs: D[c][j] = digit plane c, dword j of
 // the pair's 64 inputs; sc0/sc1 the two input block scales.
 template <int QT>
@@ -3081,9 +3089,9 @@ __global__ __launch_bounds__(kThreads, 2) void pf_down_kernel(PfDownParams a) {
 //
 // The same tiling as pf_gateup_kernel / pf_down_kernel (128-row M-tiles, four
 // waves of 32 rows, K steps of 64 with PF_K_LOOP's two steps of prefetch) with
-// a dequantiser for any of the four formats: thread t takes weight row t % 128
+// a dequantiser for Q4_K and Q6_K: thread t takes weight row t % 128
 // of the tile and, per K step, the quarters (t / 128) and (t / 128) + 2 of its
-// 64 weights (16 each).  Used for Q4_K / Q6_K; the 32-weight block formats run
+// 64 weights (16 each); the 32-weight block formats run
 // the kernels above, whose one-block-per-thread dequantiser measured faster for
 // them (a 256-row, eight-wave variant of this kernel, dequantising each tile
 // once per 256 rows, ran no faster: the loop is bound by latency, not by the
@@ -3092,8 +3100,6 @@ constexpr int kGmThreads = 256;
 constexpr int kGmQ = 512 / kGmThreads;  // dequantised quarters per thread and step
 
 // The raw bytes thread quarter bq (0..3) needs for K step kt of a weight row:
-//   Q8_0 (pair of blocks at 68 kt): the 9 dwords of block bq / 2 (load_half);
-//   Q4_0 (pair at 36 kt): the 5 dwords of block bq / 2 (load_half);
 //   Q4_K (chunk kt % 4 of super-block kt / 4): the 16-byte header and the 16
 //     bytes of q holding weights 16 (bq % 2) .. +15 of the chunk's two sub-blocks;
 //   Q6_K (weights 64 (kt % 4) .. +63 of super-block kt / 4): 20 bytes around the
@@ -3101,21 +3107,7 @@ constexpr int kGmQ = 512 / kGmThreads;  // dequantised quarters per thread and s
 //     its scale and the one holding d (addresses rounded down to a dword).
 template <int FMT>
 __device__ __forceinline__ void gm_load_raw(const uint8_t *row, int kt, int bq, uint32_t (&v)[12]) {
-  if constexpr (FMT == 8) {
-    // dwords of the 68-byte pair: v[0] = the one holding block b's d (dword 8b), v[1..5] =
-    // dwords 8b + 4 part .. +4, which hold the 16 q bytes of the quarter (block b = bq / 2,
-    // q bytes 2 + 16 part .. of the block)
-    const g_u32 *pw = (const g_u32 *)(row + (int64_t)kt * 68);
-    const int b = bq >> 1, w0 = 8 * b + 4 * (bq & 1);
-    v[0] = pw[8 * b];
-#pragma unroll
-    for (int i = 0; i < 5; ++i) v[1 + i] = pw[w0 + i];
-  } else if constexpr (FMT == 2) {
-    uint32_t t[9];
-    load_half<FMT>(row + (int64_t)kt * 36, bq >> 1, t);
-#pragma unroll
-    for (int i = 0; i < 5; ++i) v[i] = t[i];
-  } else if constexpr (FMT == 12) {
+  if constexpr (FMT == 12) {
     const uint8_t *b = row + (int64_t)(kt >> 2) * 144;
     const u32x4 hd = *(g_u32x4_a4 *)b;
     const u32x4 q = *(g_u32x4_a4 *)(b + 16 + 32 * (kt & 3) + 16 * (bq & 1));
@@ -3150,34 +3142,9 @@ __device__ __forceinline__ void gm_load_raw(const uint8_t *row, int kt, int bq, 
 template <int FMT>
 __device__ __forceinline__ void gm_dequant(const uint32_t (&v)[12], const uint8_t *row, int kt, int bq,
                                            __bf16 *dst) {
+  static_assert(FMT == 12 || FMT == 14, "K-quants");
   __bf16 o[16];
-  const int part = bq & 1;
-  if constexpr (FMT == 8) {
-    // block 0: d = bytes 0-1, its q from byte 2 (2 bytes into the window); block 1: d =
-    // bytes 34-35, its q from byte 36 (one dword into the window)
-    const int half = bq >> 1;
-    const float d = half_bits_to_float(half == 0 ? (v[0] & 0xffffu) : (v[0] >> 16));
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const uint32_t w = half == 0 ? __builtin_amdgcn_alignbyte(v[2 + j], v[1 + j], 2) : v[2 + j];
-#pragma unroll
-      for (int b = 0; b < 4; ++b) o[4 * j + b] = (__bf16)(d * (float)(int8_t)((w >> (8 * b)) & 0xffu));
-    }
-  } else if constexpr (FMT == 2) {
-    // block 0: bytes 0..19 (d = 0-1, nibbles 2..17); block 1: bytes 16..35 (d = 18-19, 20..35);
-    // part 0: the low nibbles (weights 0..15 of the block), part 1: the high ones
-    const int half = bq >> 1;
-    const float d = half_bits_to_float(half == 0 ? (v[0] & 0xffffu) : (v[0] >> 16));
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const uint32_t w = half == 0 ? __builtin_amdgcn_alignbyte(v[j + 1], v[j], 2) : v[j + 1];
-#pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        const uint32_t byte = (w >> (8 * b)) & 0xffu;
-        o[4 * j + b] = (__bf16)(d * (float)((int)(part ? byte >> 4 : byte & 0xfu) - 8));
-      }
-    }
-  } else if constexpr (FMT == 12) {
+  if constexpr (FMT == 12) {
     // sub-block 2c + (bq >> 1): low nibbles for bq < 2, high for bq >= 2
     const int j = 2 * (kt & 3) + (bq >> 1), jj = j & 3;
     const uint32_t B0 = v[1], B1 = v[2], B2 = v[3];
@@ -3854,25 +3821,16 @@ static int gm_experts(const PfWave &W, int bm, PfExperts &X) {
   return tiles;
 }
 
-// kAll: a kernel for every format; otherwise for the K-quant formats only (the
-// 32-weight formats' 256-thread grouped GEMMs are pf_gateup_kernel / pf_down_kernel).
-template <template <int> class K, bool kAll = true>
-static hipError_t gm_launch(int fmt, dim3 grid, const GmParams &a, hipStream_t s, const Timing &t,
-                            int threads = kGmThreads) {
+// The 256-thread grouped GEMM of a K-quant format (the 32-weight formats' are
+// pf_gateup_kernel / pf_down_kernel).
+template <template <int> class K>
+static hipError_t gm_launch(int fmt, dim3 grid, const GmParams &a, hipStream_t s, const Timing &t) {
   switch (fmt) {
-    case 8:
-      if constexpr (!kAll) return hipErrorInvalidValue;
-      else hipExtLaunchKernelGGL(K<8>::fn(), grid, dim3(threads), 0, s, t.start, t.stop, 0, a);
-      break;
-    case 2:
-      if constexpr (!kAll) return hipErrorInvalidValue;
-      else hipExtLaunchKernelGGL(K<2>::fn(), grid, dim3(threads), 0, s, t.start, t.stop, 0, a);
-      break;
     case 12:
-      hipExtLaunchKernelGGL(K<12>::fn(), grid, dim3(threads), 0, s, t.start, t.stop, 0, a);
+      hipExtLaunchKernelGGL(K<12>::fn(), grid, dim3(kGmThreads), 0, s, t.start, t.stop, 0, a);
       break;
     case 14:
-      hipExtLaunchKernelGGL(K<14>::fn(), grid, dim3(threads), 0, s, t.start, t.stop, 0, a);
+      hipExtLaunchKernelGGL(K<14>::fn(), grid, dim3(kGmThreads), 0, s, t.start, t.stop, 0, a);
       break;
     default:
       return hipErrorInvalidValue;
@@ -3947,7 +3905,7 @@ hipError_t launch_pf_gateup(int qtype, const PfWave &W, const int32_t *perm, con
       hipExtLaunchKernelGGL(pf_gateup_kernel<2>, dim3(tiles, I / 64), dim3(kThreads), 0, s, t.start, t.stop, 0, b);
     return hipGetLastError();
   }
-  return gm_launch<GmGateUp, false>(fmt, dim3(tiles, I / 64), a, s, t);
+  return gm_launch<GmGateUp>(fmt, dim3(tiles, I / 64), a, s, t);
 }
 
 hipError_t launch_pf_down(int qtype, const PfWave &W, const int32_t *perm, const __bf16 *ab,
@@ -3990,7 +3948,7 @@ hipError_t launch_pf_down(int qtype, const PfWave &W, const int32_t *perm, const
       hipExtLaunchKernelGGL(pf_down_kernel<2>, dim3(tiles, (H + 127) / 128), dim3(kThreads), 0, s, t.start, t.stop, 0, b);
     return hipGetLastError();
   }
-  return gm_launch<GmDown, false>(fmt, dim3(tiles, (H + 127) / 128), a, s, t);
+  return gm_launch<GmDown>(fmt, dim3(tiles, (H + 127) / 128), a, s, t);
 }
 
 hipError_t launch_pf_combine(const float *P, const float *x, float *y, int T, int H, int k,
@@ -4007,9 +3965,11 @@ hipError_t launch_token_digits(const float *x, int T, int H, bool prenorm, int8_
                      s, x, H, (int)prenorm, xq, xsc);
   return hipGetLastError();
 }
-// Enough blocks (64 tokens x slice each) for calls of middling length: with 4 slices from
-// 257 tokens on, 777 tokens made 52 blocks and took 35 us, as long as 4096 tokens (256
-// blocks, 30 us); with these a whole 777-token call takes 15 us less, one of 300 18 us.
+// More blocks (64 tokens x slice each, for every 128 experts) for calls of middling length:
+// with 4 slices from 257 tokens on, 777 tokens made 52 blocks and took 35 us, as long as 4096
+// tokens (256 blocks, 30 us); with these a whole 777-token call takes 15 us less, one of 300
+// 18 us.  The steps go by the tokens alone: at their lower ends (257, 1025, 2049 tokens) 128
+// experts make 80 to 136 blocks, fewer than compute units.
 int router_slices(int T) { return T <= kPfTok ? 64 : T <= 32 * kPfTok ? 16 : T <= 64 * kPfTok ? 8 : 4; }
 int64_t router_zbuf_floats(int64_t T, int E) {
   // the most any call of at most T tokens needs (slices * tokens is not monotonic in T)

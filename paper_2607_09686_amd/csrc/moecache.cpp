@@ -58,7 +58,7 @@ int fail(int code, const char *fmt, ...) {
 constexpr int kCopyGrid = 64;  // copy-kernel blocks: enough requests in flight to fill PCIe
 // Multi-token calls of at most this many tokens whose routed experts all fit the
 // slots run the decode GEMVs once per token instead of the MFMA grouped GEMMs
-// (whose 128-row tiles would hold a handful of rows).
+// (whose 16-row subtiles would hold a handful of rows).
 constexpr int kSmallTokens = kMtTokens;
 
 struct TimedSpan {

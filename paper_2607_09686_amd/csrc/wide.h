@@ -51,10 +51,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t wide_buffer(const void *p, uin
 // against 393), as a wave's vector instructions do not hide behind its own MFMAs.  Q6_K has
 // no slim kernels: its dequantisation is the longest, and the wide kernels' staging waves are
 // as fast at few rows and faster at many (kernels.hip, wide_launch).
-// A warm call over 128 experts of 768 x 2048 (Q8_0), gate/up + down: 4096 tokens 555 +
-// 340 us with 128-row tiles and a weight row per staging lane, 462 + 309 us wide (890
+// A warm call over 128 experts of 768 x 2048 (Q8_0), gate/up + down: 4096 tokens 536 +
+// 327 us with 128-row tiles and a weight row per staging lane, 467 + 284 us wide (883
 // TFLOP/s of gate/up MFMAs on real rows; a large library bf16 product: 1118); 61 tokens
-// 194 + 101 -> 116 + 62 us slim (3.5 TB/s of weights).
+// 198 + 104 -> 116 + 62 us slim (3.5 TB/s of weights).  Q4_K gate/up + Q6_K down: 527 + 376
+// -> 470 + 328 us; 61 tokens 178 + 117 -> 101 us slim + 81 us wide.
 // Each LDS stage is its own array, so that the compiler sees the reads of one stage not
 // alias the loads into the other.  The 1-D grid runs the column tiles of an M-tile, then
 // an expert's M-tiles, one after the other on the same XCD (block L runs on XCD L % 8), so

@@ -9,7 +9,7 @@ the slots / exceeds them) and the bf16 MFMA prefill.  Every call is compared wit
 oracle (exact oracle for the GEMV paths, bf16-weight oracle for the MFMA GEMMs): routes,
 trace and counters exact, y within 2e-3 x RMS.
 
-Also here: a prefill call with about 256 rows per expert (a second, partial 128-row tile
+Also here: a prefill call with about 256 rows per expert (two tiles of at most 144 rows
 of every expert's GEMMs) compared on every row, and slots poisoned with 0xFF bytes before
 use (every slot scale reads NaN until the expert is copied in), so that a read of a slot
 before its copy has landed would show up as a non-finite output.
@@ -86,7 +86,7 @@ def test_edge_blocks_prefill(qtype, regime):
 @pytest.mark.parametrize("qtype", ["q8_0", "q4_0"])
 def test_prefill_rows_past_first_tile(qtype):
     """2048 tokens over 16 experts, top-2: about 256 rows per expert, so every expert's
-    GEMMs run a full 128-row tile and a partial second (or third) one; y of every token is
+    GEMMs run two (or three) tiles, the last one partial; y of every token is
     compared, with 6 slots (waves of slot reuse) and with every expert resident."""
     wl = edge_workload(qtype, n_layers=1, hidden=1024, inter=384, top_k=2)
     store = store_buffer(wl)

@@ -81,8 +81,8 @@ def test_kquant_prefill_and_small_calls(qtype):
 
 @pytest.mark.parametrize("qtype", ["q4_k_m", "q6_k"])
 def test_kquant_prefill_rows_past_first_tile(qtype):
-    """2048 tokens, 16 experts, top-2: about 256 rows per expert, a full 256-row tile and a
-    partial second one for many experts; every token's y compared, hand-worked super-blocks."""
+    """2048 tokens, 16 experts, top-2: about 256 rows per expert, two (or three) tiles of at
+    most 144 rows, the last one partial; every token's y compared, hand-worked super-blocks."""
     wl = kq_workload(qtype, n_layers=1, hidden=1024, inter=512, top_k=2)
     keep, ptr, arr = store_buffer(wl)
     kquant_golden_store(arr, wl, seed=3)

@@ -61,17 +61,28 @@ def verify_windows(n_tokens, horizon, passes):
     return steps
 
 
+def kernel_sources_sha256_16():
+    """Hash of every device source (csrc/*.hip and their headers, in name order): what a profile
+    was measured on."""
+    import hashlib
+    csrc = os.path.join(ROOT, "paper_2607_09686_amd", "csrc")
+    h = hashlib.sha256()
+    for name in sorted(os.listdir(csrc)):
+        if name.endswith((".hip", ".h")):
+            h.update(name.encode() + b"\0")
+            with open(os.path.join(csrc, name), "rb") as f:
+                h.update(f.read() + b"\0")
+    return h.hexdigest()[:16]
+
+
 def measured_traffic(args, name, wl, budget):
     """Bytes per launch of a kernel from profiles/<name>_traffic.json, or None when the file is
-    missing or was measured on another kernels.hip, workload, budget or policy."""
-    import hashlib
+    missing or was measured on other device sources, another workload, budget or policy."""
     path = os.path.join(args.profiles, name + "_traffic.json")
     if not os.path.exists(path) or budget != wl.budget_slots or args.policy != "lru":
         return None
     t = json.load(open(path))
-    src = os.path.join(ROOT, "paper_2607_09686_amd", "csrc", "kernels.hip")
-    cur = hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
-    if t.get("kernels_hip_sha256_16") != cur or t.get("workload") != wl.name:
+    if t.get("kernel_sources_sha256_16") != kernel_sources_sha256_16() or t.get("workload") != wl.name:
         return None
     return t["traffic_bytes_per_launch"]
 
@@ -115,7 +126,7 @@ def parse():
     ap.add_argument("--profiles", default=os.path.join(ROOT, "profiles"),
                     help="directory of the measured bytes per launch (rocprofv3 --pmc) of the "
                          "roofline kernels; a file is used only if it was taken on the current "
-                         "kernels.hip and this workload")
+                         "device sources and this workload")
     ap.add_argument("--hbm-probe", action="store_true",
                     help="decode: after the run, launch a plain HBM read of the down GEMV's bytes "
                          "per launch (256, 512 and 2048 blocks, 52 launches each) and an empty "
@@ -430,13 +441,10 @@ def main():
         # of its duration: the rocprofv3 kernel-trace durations of the down GEMV, a plain
         # read of its bytes in one launch and an empty launch (one clock for all three),
         # from profiles/decode_hbm_reference.json when it was taken on the current kernels
-        import hashlib
         path = os.path.join(args.profiles, "decode_hbm_reference.json")
         if os.path.exists(path):
             ref = json.load(open(path))
-            src = os.path.join(ROOT, "paper_2607_09686_amd", "csrc", "kernels.hip")
-            cur = hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
-            if ref.get("kernels_hip_sha256_16") == cur and wl.name in ref:
+            if ref.get("kernel_sources_sha256_16") == kernel_sources_sha256_16() and wl.name in ref:
                 result["extra"]["hbm_launch_reference"] = dict(ref[wl.name], clock=ref["clock"])
         st = stats.get("down") if timing else None
         if args.hbm_probe and st and st["launches"]:
